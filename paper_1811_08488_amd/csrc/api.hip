@@ -119,8 +119,8 @@ struct BlockGeom {
   std::vector<int> be_off, o1_off, e2_off;   // padded offsets, size nb+1
   std::vector<int> be_n, o1_n, e2_n;         // true counts
   std::vector<int> be_lex, o1_lex, e2_lex;   // lex per padded entry (-1 padding)
-  DBuf d_be_cb, d_be_blk, d_be_nbr, d_be_e2, d_o1_cb, d_o1_nbr_be, d_o1_nbr_e2, d_e2_cb, d_e2_nbr, d_e2_be, d_be_off,
-      d_e2_off;
+  DBuf d_be_cb, d_be_blk, d_be_nbr, d_be_e2, d_o1_nbr_be, d_o1_nbr_e2, d_e2_nbr, d_e2_be, d_be_off, d_e2_off;
+  DBuf d_be_lk, d_o1_lk, d_e2_lk;  // position of a site's links (-1: padding)
   // work vectors (inner precision); `gen` changes whenever they are reallocated
   // or cleared for another layout, so that graphs captured on them are never replayed
   int vprec = -1, vnrhs = 0;
@@ -181,9 +181,11 @@ struct mspcg_handle {
   // captured preconditioner launches, keyed by everything they bake in
   std::map<std::vector<intptr_t>, hipGraphExec_t> graphs;
   double alpha5 = 0, beta5 = 0;  // M_5 = alpha5 - beta5 P_chi
-  // global tables per parity: site list (identity), neighbours (cb of the other parity)
+  // global tables per parity: site list (cb in the order of visit), neighbours (cb of the other parity) by
+  // list position, lex indices by cb
   DBuf d_order[2], d_nbr[2], d_lex[2], d_nbrlex[2];
   std::vector<int> lex_of_cb[2], nbr_cb[2];
+  std::vector<int> pos_of_cb[2];  // position of a site in the order its parity is visited (links are packed in it)
   DBuf links[4][2];
   bool links_ok[4] = {false, false, false, false};
   DBuf d_gauge;
@@ -278,8 +280,8 @@ void ensure_links(mspcg_handle *h, int prec, hipStream_t st) {
   if (h->links_ok[prec]) return;
   for (int p = 0; p < 2; ++p) {
     h->links[prec][p].ensure((size_t)h->Vh * 8 * 18 * prec_bytes(prec));
-    HIPCHK(pack_links(prec, h->links[prec][p].p, h->d_gauge.as<double>(), h->d_lex[p].as<int>(),
-                      h->d_nbrlex[p].as<int>(), p, h->Vh, h->par.L[3], h->Lxyz, (double)h->par.t_bc, st));
+    HIPCHK(pack_links(prec, h->links[prec][p].p, h->d_gauge.as<double>(), h->d_order[p].as<int>(),
+                      h->d_lex[p].as<int>(), h->d_nbrlex[p].as<int>(), h->Vh, h->par.L[3], h->Lxyz, (double)h->par.t_bc, st));
   }
   h->links_ok[prec] = true;
 }
@@ -452,7 +454,7 @@ BlockGeom *get_blocks(mspcg_handle *h, const int nblk[4], int no_snake, hipStrea
   bg->nb = nblk[0] * nblk[1] * nblk[2] * nblk[3];
   const int V = h->V;
   std::vector<int> e2_of_lex(V, -1), o1_of_lex(V, -1);  // per-block scratch maps
-  std::vector<int> be_cb, be_blk, be_nbr, be_e2, o1_cb, o1_nbr_be, o1_nbr_e2, e2_cb, e2_nbr, e2_be;
+  std::vector<int> be_cb, be_blk, be_nbr, be_e2, be_lk, o1_nbr_be, o1_nbr_e2, o1_lk, e2_nbr, e2_be, e2_lk;
   bg->be_off.push_back(0);
   bg->o1_off.push_back(0);
   bg->e2_off.push_back(0);
@@ -514,12 +516,12 @@ BlockGeom *get_blocks(mspcg_handle *h, const int nblk[4], int no_snake, hipStrea
     for (int i = 0; i < pe2; ++i) {
       if (i < ne2) {
         const int g = loc_e2[i];
-        e2_cb.push_back(g >> 1);
+        e2_lk.push_back(h->pos_of_cb[0][g >> 1]);
         for (int d = 0; d < 8; ++d) e2_nbr.push_back(o1_of_lex[nb_lex(g, d)]);
         e2_be.push_back(be_of_e2[i]);
         bg->e2_lex.push_back(g);
       } else {
-        e2_cb.push_back(-1);
+        e2_lk.push_back(-1);
         for (int d = 0; d < 8; ++d) e2_nbr.push_back(-1);
         e2_be.push_back(-1);
         bg->e2_lex.push_back(-1);
@@ -529,7 +531,7 @@ BlockGeom *get_blocks(mspcg_handle *h, const int nblk[4], int no_snake, hipStrea
     for (int i = 0; i < po1; ++i) {
       if (i < no1) {
         const int g = loc_o1[i];
-        o1_cb.push_back(g >> 1);
+        o1_lk.push_back(h->pos_of_cb[1][g >> 1]);
         for (int d = 0; d < 8; ++d) {
           const int e = e2_of_lex[nb_lex(g, d)];
           o1_nbr_e2.push_back(e);
@@ -537,7 +539,7 @@ BlockGeom *get_blocks(mspcg_handle *h, const int nblk[4], int no_snake, hipStrea
         }
         bg->o1_lex.push_back(g);
       } else {
-        o1_cb.push_back(-1);
+        o1_lk.push_back(-1);
         for (int d = 0; d < 8; ++d) { o1_nbr_e2.push_back(-1); o1_nbr_be.push_back(-1); }
         bg->o1_lex.push_back(-1);
       }
@@ -550,6 +552,7 @@ BlockGeom *get_blocks(mspcg_handle *h, const int nblk[4], int no_snake, hipStrea
         const int g = loc_e2[i];
         if (g != loc_be[k]) fail(MSPCG_EINVAL, "internal: block ordering mismatch");
         be_cb.push_back(g >> 1);
+        be_lk.push_back(h->pos_of_cb[0][g >> 1]);
         be_blk.push_back(b);
         be_e2.push_back(e20 + i);
         for (int d = 0; d < 8; ++d) be_nbr.push_back(e2_nbr[(size_t)(e20 + i) * 8 + d]);
@@ -558,6 +561,7 @@ BlockGeom *get_blocks(mspcg_handle *h, const int nblk[4], int no_snake, hipStrea
       }
       for (int i = nbe; i < pbe; ++i) {
         be_cb.push_back(-1);
+        be_lk.push_back(-1);
         be_blk.push_back(-1);
         be_e2.push_back(-1);
         for (int d = 0; d < 8; ++d) be_nbr.push_back(-1);
@@ -607,12 +611,13 @@ BlockGeom *get_blocks(mspcg_handle *h, const int nblk[4], int no_snake, hipStrea
   upload(bg->d_be_blk, be_blk, st);
   upload(bg->d_be_nbr, be_nbr, st);
   upload(bg->d_be_e2, be_e2, st);
-  upload(bg->d_o1_cb, o1_cb, st);
   upload(bg->d_o1_nbr_be, o1_nbr_be, st);
   upload(bg->d_o1_nbr_e2, o1_nbr_e2, st);
-  upload(bg->d_e2_cb, e2_cb, st);
   upload(bg->d_e2_nbr, e2_nbr, st);
   upload(bg->d_e2_be, e2_be, st);
+  upload(bg->d_be_lk, be_lk, st);
+  upload(bg->d_o1_lk, o1_lk, st);
+  upload(bg->d_e2_lk, e2_lk, st);
   upload(bg->d_be_off, bg->be_off, st);
   upload(bg->d_e2_off, bg->e2_off, st);
   HIPCHK(hipStreamSynchronize(st));
@@ -679,11 +684,11 @@ void ensure_block_vecs(mspcg_handle *h, BlockGeom *bg, int prec, int nrhs) {
 }
 
 // Block-domain hop arguments (lists, tables and fields of one hop of A_s).
-HopArgs block_hop_args(mspcg_handle *h, int nrhs, int nsites, const int *site_cb, const int *nbr, const Vec &in,
+HopArgs block_hop_args(mspcg_handle *h, int nrhs, int nsites, const int *site_lk, const int *nbr, const Vec &in,
                        const Vec &out, int out_parity, int prec) {
   HopArgs a = base_args(h, nrhs);
   a.nsites = nsites;
-  a.site_cb = site_cb;
+  a.site_cb = site_lk;
   a.nbr = nbr;
   a.in = in.data;
   a.in_norm = in.norm;
@@ -705,14 +710,14 @@ HopArgs block_hop_args(mspcg_handle *h, int nrhs, int nsites, const int *site_cb
 int block_hop(mspcg_handle *h, BlockGeom *bg, int prec, int nrhs, int which, const Vec &in, const Vec &in_mp,
               const Vec &out, double *partial, hipStream_t st, const double *upd_scal = nullptr) {
   if (which == 1) {  // c = M_phi M_5^{-1} (-1/2 H M_phi in) on O1
-    HopArgs a1 = block_hop_args(h, nrhs, bg->o1_tot, bg->d_o1_cb.as<int>(), bg->d_o1_nbr_be.as<int>(), in_mp,
+    HopArgs a1 = block_hop_args(h, nrhs, bg->o1_tot, bg->d_o1_lk.as<int>(), bg->d_o1_nbr_be.as<int>(), in_mp,
                                 bg->o1v.v, 1, prec);
     a1.scale = -0.5;
     a1.mat = h->x1.ptr(prec);
     return run_hop(h, 1, prec, 0, 0, EPI_M5INV, 0, 0, a1, st);
   }
   if (which == 2) {  // y = M_5 in + 1/2 H c on E2
-    HopArgs a2 = block_hop_args(h, nrhs, bg->e2_tot, bg->d_e2_cb.as<int>(), bg->d_e2_nbr.as<int>(), bg->o1v.v,
+    HopArgs a2 = block_hop_args(h, nrhs, bg->e2_tot, bg->d_e2_lk.as<int>(), bg->d_e2_nbr.as<int>(), bg->o1v.v,
                                 bg->e2v.v, 0, prec);
     a2.scale = 0.5;
     a2.other = in.data;
@@ -725,14 +730,14 @@ int block_hop(mspcg_handle *h, BlockGeom *bg, int prec, int nrhs, int which, con
     return run_hop(h, 2, prec, 0, 0, EPI_M5_OTHER, partial ? 1 : 0, 0, a2, st);
   }
   if (which == 3) {  // f = M_5^{-+} M_phi^+ (-1/2 H^+ y) on O1
-    HopArgs a3 = block_hop_args(h, nrhs, bg->o1_tot, bg->d_o1_cb.as<int>(), bg->d_o1_nbr_e2.as<int>(), bg->e2v.v,
+    HopArgs a3 = block_hop_args(h, nrhs, bg->o1_tot, bg->d_o1_lk.as<int>(), bg->d_o1_nbr_e2.as<int>(), bg->e2v.v,
                                 bg->o1v.v, 1, prec);
     a3.scale = -0.5;
     a3.mat = h->x1.ptr(prec);  // (the daggered hop applies the transpose)
     return run_hop(h, 3, prec, 1, 0, EPI_M5INV, 0, 0, a3, st);
   }
   // out = M_5^+ y + 1/2 M_phi^+ H^+ f on B_e
-  HopArgs a4 = block_hop_args(h, nrhs, bg->be_tot, bg->d_be_cb.as<int>(), bg->d_be_nbr.as<int>(), bg->o1v.v, out,
+  HopArgs a4 = block_hop_args(h, nrhs, bg->be_tot, bg->d_be_lk.as<int>(), bg->d_be_nbr.as<int>(), bg->o1v.v, out,
                               0, prec);
   a4.scale = 0.5;
   a4.other = bg->e2v.v.data;
@@ -1259,11 +1264,13 @@ mspcg_status mspcg_create(mspcg_handle **hp, const mspcg_dwf *p, const double *g
                     if (((x + y + z + t) & 1) == par) order.push_back((x + L[0] * (y + L[1] * (z + L[2] * t))) >> 1);
       if ((int)order.size() != h->Vh) fail(MSPCG_EINVAL, "internal: site order incomplete");
       upload(h->d_order[par], order, st);
+      h->pos_of_cb[par].resize(h->Vh);
+      for (int i = 0; i < h->Vh; ++i) h->pos_of_cb[par][order[i]] = i;
     }
     for (int par = 0; par < 2; ++par) {
       auto &lex = h->lex_of_cb[par];
       auto &nbr = h->nbr_cb[par];
-      std::vector<int> nbrlex((size_t)h->Vh * 8);
+      std::vector<int> nbrlex((size_t)h->Vh * 8), nbr_list((size_t)h->Vh * 8);
       lex.resize(h->Vh);
       nbr.resize((size_t)h->Vh * 8);
       for (int cb = 0; cb < h->Vh; ++cb) {
@@ -1281,10 +1288,11 @@ mspcg_status mspcg_create(mspcg_handle **hp, const mspcg_dwf *p, const double *g
           const int yl = y[0] + L[0] * (y[1] + L[1] * (y[2] + L[2] * y[3]));
           nbrlex[(size_t)cb * 8 + d] = yl;
           nbr[(size_t)cb * 8 + d] = yl >> 1;
+          nbr_list[(size_t)h->pos_of_cb[par][cb] * 8 + d] = yl >> 1;
         }
       }
       upload(h->d_lex[par], lex, st);
-      upload(h->d_nbr[par], nbr, st);
+      upload(h->d_nbr[par], nbr_list, st);
       upload(h->d_nbrlex[par], nbrlex, st);
     }
     // gauge copy (physical links) for repacking in any precision

@@ -36,17 +36,19 @@ struct Vec {
 struct HopArgs {
   int nsites;          // output list length
   int Ls, nrhs, nsite_wg;
-  const int *site_cb;  // [nsites] cb of the output site in the full lattice (-1: padding)
-  const int *nbr;      // [site][8] input index of neighbour d = 2 mu + (0 fwd, 1 bwd); indexed by cb for the
-                       // full lattice, by list position for block domains, where a neighbour outside the
-                       // domain is stored as -1 - alt (alt: an input index whose data is loaded with weight 0)
+  const int *site_cb;  // [nsites] full lattice: cb of the output site; block domains: the position of its
+                       // links in the full lattice's list (-1: padding)
+  const int *nbr;      // [list position][8] input index of neighbour d = 2 mu + (0 fwd, 1 bwd); in block domains
+                       // a neighbour outside the domain is stored as -1 - alt (alt: an input index whose data is
+                       // loaded with weight 0)
   const void *in;
   const float *in_norm;
   long long in_stride;
   void *out;
   float *out_norm;
   long long out_stride;
-  const void *links;   // [cb][8][18] for the output parity; sign of the time boundary folded in
+  const void *links;   // [position in the full lattice's list][8][18] for the output parity; sign of the time
+                       // boundary folded in
   const void *other;   // EPI_M5_OTHER / EPI_M5DAG_MPHIDAG operand
   const float *other_norm;
   long long other_stride;
@@ -163,8 +165,8 @@ hipError_t block_update_xp(int prec, const BlockArgs &b, const Vec &x, const Vec
 constexpr int kScal = 4;
 
 // Pack the physical FP64 gauge field [lex][mu][3][3] into per-parity site-packed
-// links [cb][8][18] (forward U_mu(x), backward U_mu(x-mu)^+, time boundary sign folded).
-hipError_t pack_links(int prec, void *out, const double *gauge, const int *lex_of_cb, const int *nbr_lex, int parity,
-                      int Vh, int Lt, int Lxyz, double tbc, hipStream_t st);
+// links [position in the site order][8][18] (forward U_mu(x), backward U_mu(x-mu)^+, time boundary sign folded).
+hipError_t pack_links(int prec, void *out, const double *gauge, const int *order, const int *lex_of_cb,
+                      const int *nbr_lex, int Vh, int Lt, int Lxyz, double tbc, hipStream_t st);
 
 }  // namespace mspcg

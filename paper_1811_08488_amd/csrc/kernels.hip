@@ -498,9 +498,10 @@ __device__ inline void wg_partial(double *ldsd, int nthr, int tid, int Ls, int n
 // for the daggered hop g5 H g5 = H^+.
 // Workgroup = (s, rhs, site) threads: threadIdx.x = s, .y = rhs, .z = site.
 // GLOBAL: the output list is the whole parity (site_cb a permutation of cb in
-// column-sweep order); neighbour tables, outputs and the `other`/dot operands are
-// indexed by cb.  Otherwise (block domains) they are indexed by the position
-// in the list, and neighbours outside the domain enter with weight zero.
+// column-sweep order); outputs and the `other`/dot operands are indexed by cb,
+// neighbour tables and links by the position in the list.  Otherwise (block
+// domains) all but the links are indexed by the position in the list, and
+// neighbours outside the domain enter with weight zero.
 // Occupancy the register allocation of the hop kernel is held to (waves per SIMD).
 // (the LDS exchange keeps more values live; FP64 doubles every register)
 template <typename S, int XM> struct HopWaves { static constexpr int value = XM == kXLds ? 3 : 4; };
@@ -534,11 +535,57 @@ __global__ void __launch_bounds__(256, (HopWaves<S, XM>::value)) hop_kernel(cons
   R *lds = Lk + nsw * 144;              // exchange rows [nthr][kRow] (LDS mode, M_5^{-1})
   const int tile = xcd_tile(blockIdx.x, gridDim.x);
   const int site = tile * nsw + sl;
-  const int cbr = (site < a.nsites) ? a.site_cb[site] : -1;
+  // The chain of dependent loads before the first spinor bounds a launch that
+  // does not fill the chip several times over, and costs a wave of a full one
+  // as much as two directions of the loop below: the neighbour row depends on
+  // the list position alone, and with the full lattice so do the links (packed
+  // in list order), so index, neighbour and link loads are all in flight at
+  // once and only the spinors wait for one of them.
+  const bool listed = site < a.nsites;
+  const int row = listed ? site : 0;  // (inactive lanes compute on valid data and store nothing)
+  const int cbr = listed ? a.site_cb[row] : -1;  // full lattice: cb; block domains: position of the site's links
   const bool has_upd = !GLOBAL && a.upd_scal;
-  const int ublk = (has_upd && site < a.nsites) ? a.upd_blk[site] : -1;
-  const bool active = lane_ok && cbr >= 0;
-  const int cb = active ? cbr : 0;
+  const int ublk = (has_upd && listed) ? a.upd_blk[row] : -1;
+  const bool active = lane_ok && (GLOBAL ? listed : cbr >= 0);
+
+  // The eight neighbour indices are loaded once, with two 16-byte loads, and
+  // kept in registers (rotated by two per direction pair below): no spinor
+  // load ever waits for an index load issued after an earlier spinor load.
+  // Block domains: a neighbour outside the domain is stored as -1 - n with n
+  // an in-domain substitute whose data enters with weight zero (bit d of
+  // outm).
+  const int4 *nb4 = reinterpret_cast<const int4 *>(a.nbr + (size_t)row * 8);
+  const int4 q0 = nb4[0], q1 = nb4[1];
+
+  // the links of all sites of the workgroup, staged once into LDS with
+  // 16-byte loads (every link is used by all Ls x nrhs lanes of its site); the
+  // lanes of a site stage that site's links.  The first kLinkBatch words of a
+  // lane are requested together (all of them for Ls x nrhs >= 8): loaded one
+  // after the other they were 3 to 9 memory latencies in a row (FP64, Ls = 24
+  // to 8).  With the independent index loads: FP64 dslash_eo on 8^4 x 8 11.7 ->
+  // 9.2 us, FP64 A on 24^3 x 64 x 24 7221 -> 6773 us.
+  constexpr bool kH16 = std::is_same<S, _Float16>::value;
+  constexpr int per = 16 / sizeof(S);
+  constexpr int nchunk = 144 / per;
+  constexpr int kLinkBatch = (nchunk + 7) / 8;
+  const int lstep = Ls * nrhs, lfirst = s + Ls * r;
+  const uint4 *lsrc = reinterpret_cast<const uint4 *>(a.links) +
+                      (size_t)(GLOBAL ? row : (cbr >= 0 ? cbr : 0)) * nchunk;
+  uint4 lq[kLinkBatch];
+  auto load_links = [&] {
+#pragma unroll
+    for (int j = 0; j < kLinkBatch; ++j)
+      if (j * lstep < nchunk) lq[j] = lsrc[min(lfirst + j * lstep, nchunk - 1)];
+  };
+  auto stage_links = [&](int c, uint4 q) {
+    if constexpr (kH16)  // F16: (A, B) pairs for the packed link product
+      link_pairs_h16(q, reinterpret_cast<uint32_t *>(Lk) + sl * 144 + c * 8);
+    else
+      widen16<R>(reinterpret_cast<const S *>(&q), Lk + sl * 144 + c * per);
+  };
+  if (GLOBAL) load_links();
+
+  const int cb = GLOBAL ? cbr : 0;
   const int self = GLOBAL ? cb : site;  // index of this site in tables and outputs
   // A fused CG residual update (block domains, upd_scal set) stores
   // out - alpha (result): alpha is requested here, long before it is needed,
@@ -548,18 +595,9 @@ __global__ void __launch_bounds__(256, (HopWaves<S, XM>::value)) hop_kernel(cons
   double alpha_u = 0;
   if (upd) alpha_u = a.upd_scal[((size_t)ublk * nrhs + r) * kScal + 1];
 
-  // The eight neighbour indices are loaded once, with two 16-byte loads, and
-  // kept in registers (rotated by two per direction pair below): no spinor
-  // load ever waits for an index load issued after an earlier spinor load.
-  // Block domains: a neighbour outside the domain is stored as -1 - n with n
-  // an in-domain substitute whose data enters with weight zero (bit d of
-  // outm).  Inactive lanes take the neighbours of row 0: they compute on valid
-  // data and store nothing.
   int nbw[8];
   int outm = 0;
   {
-    const int4 *nb4 = reinterpret_cast<const int4 *>(a.nbr + (size_t)(active ? self : 0) * 8);
-    const int4 q0 = nb4[0], q1 = nb4[1];
     const int qa[8] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w};
 #pragma unroll
     for (int d = 0; d < 8; ++d) {
@@ -571,7 +609,6 @@ __global__ void __launch_bounds__(256, (HopWaves<S, XM>::value)) hop_kernel(cons
       }
     }
   }
-  // the first neighbour spinor is requested before anything else waits
   const S *in = reinterpret_cast<const S *>(a.in);
   const size_t rin = (size_t)r * a.in_stride;
   // neighbour n of this lane: chunk 0 at in_s + n * sstride, its chunks cstride
@@ -588,22 +625,14 @@ __global__ void __launch_bounds__(256, (HopWaves<S, XM>::value)) hop_kernel(cons
   RawSite<S> cur, nxt;
   load_nbr(cur, nbw[0]);
 
-  // the links of all sites of the workgroup, staged once into LDS with
-  // 16-byte loads (every link is used by all Ls x nrhs lanes of its site);
-  // the lanes of a site stage that site's links, so no further index is read
-  constexpr bool kH16 = std::is_same<S, _Float16>::value;
+  if (!GLOBAL) load_links();
   if (lane_ok) {
-    const S *links = reinterpret_cast<const S *>(a.links);
-    constexpr int per = 16 / sizeof(S);
-    constexpr int nchunk = 144 / per;
-    const S *src = links + (size_t)(cbr >= 0 ? cbr : 0) * 144;
-    for (int c = s + Ls * r; c < nchunk; c += Ls * nrhs) {
-      if constexpr (kH16)  // F16: (A, B) pairs for the packed link product
-        link_pairs_h16(*reinterpret_cast<const uint4 *>(src + c * per),
-                       reinterpret_cast<uint32_t *>(Lk) + sl * 144 + c * 8);
-      else
-        widen16<R>(src + c * per, Lk + sl * 144 + c * per);
+#pragma unroll
+    for (int j = 0; j < kLinkBatch; ++j) {
+      const int c = lfirst + j * lstep;
+      if (c < nchunk) stage_links(c, lq[j]);
     }
+    for (int c = lfirst + kLinkBatch * lstep; c < nchunk; c += lstep) stage_links(c, lsrc[c]);
   }
   __syncthreads();
 
@@ -1401,11 +1430,11 @@ hipError_t block_update_xp(int prec, const BlockArgs &b, const Vec &x, const Vec
 
 // ---------------------------------------------------------------- link packing
 template <typename S>
-__global__ void k_pack_links(S *out, const double *gauge, const int *lex_of_cb, const int *nbr_lex, int Vh, int Lt,
-                             int Lxyz, double tbc) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;  // (cb, d)
+__global__ void k_pack_links(S *out, const double *gauge, const int *order, const int *lex_of_cb, const int *nbr_lex,
+                             int Vh, int Lt, int Lxyz, double tbc) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;  // (list position, d)
   if (i >= Vh * 8) return;
-  const int cb = i >> 3, d = i & 7, mu = d >> 1, bw = d & 1;
+  const int cb = order[i >> 3], d = i & 7, mu = d >> 1, bw = d & 1;
   const int x = lex_of_cb[cb];
   const int t = x / Lxyz;
   const int src = bw ? nbr_lex[(size_t)cb * 8 + d] : x;
@@ -1429,12 +1458,12 @@ __global__ void k_pack_links(S *out, const double *gauge, const int *lex_of_cb, 
     }
 }
 
-hipError_t pack_links(int prec, void *out, const double *gauge, const int *lex_of_cb, const int *nbr_lex, int parity,
-                      int Vh, int Lt, int Lxyz, double tbc, hipStream_t st) {
-  (void)parity;
+hipError_t pack_links(int prec, void *out, const double *gauge, const int *order, const int *lex_of_cb,
+                      const int *nbr_lex, int Vh, int Lt, int Lxyz, double tbc, hipStream_t st) {
   const int n = Vh * 8, blk = 256;
   MSPCG_PREC_SWITCH(prec, hipLaunchKernelGGL(k_pack_links<S>, dim3((n + blk - 1) / blk), dim3(blk), 0, st,
-                                             reinterpret_cast<S *>(out), gauge, lex_of_cb, nbr_lex, Vh, Lt, Lxyz, tbc));
+                                             reinterpret_cast<S *>(out), gauge, order, lex_of_cb, nbr_lex, Vh, Lt, Lxyz,
+                                             tbc));
   return hipGetLastError();
 }
 
