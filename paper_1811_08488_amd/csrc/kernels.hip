@@ -1015,8 +1015,8 @@ __global__ void __launch_bounds__(kBlasWG) k_update_xr(double *xv, double *rv, c
     const double2 pi = p[i], qi = q[i];
     xi.x += al * pi.x; xi.y += al * pi.y;
     ri.x -= al * qi.x; ri.y -= al * qi.y;
-    x[i] = xi;
-    rr[i] = ri;
+    store16(x + i, xi);
+    store16(rr + i, ri);
     acc += ri.x * ri.x + ri.y * ri.y;
   }
   block_sum_store(acc, partial + (size_t)blockIdx.x * gridDim.y + r);
@@ -1039,7 +1039,7 @@ __global__ void __launch_bounds__(kBlasWG) k_xpay(double *pv, const double *zv, 
     const double2 zi = z[i];
     pi.x = zi.x + be * pi.x;
     pi.y = zi.y + be * pi.y;
-    p[i] = pi;
+    store16(p + i, pi);
   }
 }
 
@@ -1057,7 +1057,7 @@ __global__ void __launch_bounds__(kBlasWG) k_axpby(double *ov, double a, const d
   const long long n2 = n / 2;
   for (long long i = (long long)blockIdx.x * kBlasWG + threadIdx.x; i < n2; i += (long long)kBlasGrid * kBlasWG) {
     const double2 xi = x[i], yi = y[i];
-    o[i] = make_double2(a * xi.x + b * yi.x, a * xi.y + b * yi.y);
+    store16(o + i, make_double2(a * xi.x + b * yi.x, a * xi.y + b * yi.y));
   }
 }
 
