@@ -201,10 +201,18 @@ struct mspcg_handle {
   std::map<std::vector<int>, int> tuned;
   bool autotune = true;
   int verbose = 0;  // MSPCG_VERBOSE=n: the solvers report progress on stderr every n outer iterations
+  // |r|^2 of the solvers' last two iterations, written by the device; a value
+  // is complete once its tag shows the iteration's number (never reused)
+  struct HostSlots {
+    double rr[2][MSPCG_MAX_NRHS];
+    int tag[2][MSPCG_MAX_NRHS];
+  } *slots = nullptr;
+  int next_tag = 0;
   ~mspcg_handle() {
     if (work) (void)hipStreamSynchronize(work);
     for (auto &g : graphs) (void)hipGraphExecDestroy(g.second);
     if (work) (void)hipStreamDestroy(work);
+    if (slots) (void)hipHostFree(slots);
   }
 };
 
@@ -380,11 +388,8 @@ int run_hop(mspcg_handle *h, int list_kind, int prec, int dag, int pre, int epi,
 }
 
 // Full-lattice hop: output parity p (site list = all cb), input parity 1-p.
-int global_hop(mspcg_handle *h, int prec, int nrhs, int p, const Vec &out, const Vec &in, int dag, int pre, int epi,
-               double scale, const Mat5 *mat, const Vec *other, double *partial, const Vec *dotw,
-               hipStream_t st, bool may_tune = true) {
-  if (may_tune) ensure_links(h, prec, st);
-  else if (!h->links_ok[prec]) fail(MSPCG_EUNSUPPORTED, "links of this precision have not been prepared");
+HopArgs global_hop_args(mspcg_handle *h, int prec, int nrhs, int p, const Vec &out, const Vec &in, double scale,
+                        const Mat5 *mat, const Vec *other) {
   HopArgs a = base_args(h, nrhs);
   a.nsites = h->Vh;
   a.site_cb = h->d_order[p].as<int>();
@@ -403,13 +408,40 @@ int global_hop(mspcg_handle *h, int prec, int nrhs, int p, const Vec &out, const
     a.other_norm = other->norm;
     a.other_stride = h->Vh;
   }
+  return a;
+}
+
+// partial: per-workgroup sums of Re<dotw, out>, or of |out|^2 without dotw
+int global_hop(mspcg_handle *h, int prec, int nrhs, int p, const Vec &out, const Vec &in, int dag, int pre, int epi,
+               double scale, const Mat5 *mat, const Vec *other, double *partial, const Vec *dotw,
+               hipStream_t st, bool may_tune = true) {
+  if (may_tune) ensure_links(h, prec, st);
+  else if (!h->links_ok[prec]) fail(MSPCG_EUNSUPPORTED, "links of this precision have not been prepared");
+  HopArgs a = global_hop_args(h, prec, nrhs, p, out, in, scale, mat, other);
   if (partial) {
     a.partial = partial;
-    a.dotw = dotw->data;
-    a.dotw_norm = dotw->norm;
-    a.dotw_stride = h->Vh;
+    if (dotw) {
+      a.dotw = dotw->data;
+      a.dotw_norm = dotw->norm;
+      a.dotw_stride = h->Vh;
+    }
   }
   return run_hop(h, 0, prec, dag, pre, epi, partial ? 1 : 0, 1, a, st, may_tune);
+}
+
+// The last hop of A updating the residual of the FP64 solvers in place:
+// r <- r - alpha (M_5^+ y + 1/2 M_phi^+ H^+ f), per-workgroup |r|^2 into
+// `partial`.  Its launch must not be repeated: the shape is tuned on the same
+// kernel writing into `scratch`.
+int global_update_hop(mspcg_handle *h, int nrhs, const Vec &r, const Vec &scratch, const Vec &f, const Vec &y,
+                      const double *alpha, double *partial, hipStream_t st) {
+  HopArgs a = global_hop_args(h, MSPCG_F64, nrhs, 0, scratch, f, 0.5, nullptr, &y);
+  a.partial = partial;
+  if (h->tuned.find(hop_key(0, MSPCG_F64, 1, 0, EPI_M5DAG_MPHIDAG, 1, 1, a)) == h->tuned.end())
+    (void)run_hop(h, 0, MSPCG_F64, 1, 0, EPI_M5DAG_MPHIDAG, 1, 1, a, st);
+  a.out = r.data;
+  a.upd_scal = alpha;
+  return run_hop(h, 0, MSPCG_F64, 1, 0, EPI_M5DAG_MPHIDAG, 1, 1, a, st, false);
 }
 
 // out_e = D_PC^+ D_PC in_e (all four hops fused with their fifth-dimension
@@ -971,6 +1003,15 @@ mspcg_status solve(mspcg_handle *h, mspcg_field *x, const mspcg_field *b, const 
     // the caller's fields may still be written by work on other streams
     HIPCHK(hipDeviceSynchronize());
     hipStream_t st = h->work;
+    // however the solve ends, nothing of it is left running on the caller's fields
+    struct Drain {
+      hipStream_t st;
+      ~Drain() { (void)hipStreamSynchronize(st); }
+    } drain{st};
+    if (!h->slots) {
+      HIPCHK(hipHostMalloc(reinterpret_cast<void **>(&h->slots), sizeof(*h->slots)));
+      std::memset(h->slots, 0, sizeof(*h->slots));
+    }
     const int nrhs = b->nrhs, Ls = h->par.Ls;
     const long long n = (long long)h->Vh * Ls * 24;
     BlockGeom *bg = pc ? get_blocks(h, pc->nblk, pc->no_snake, st) : nullptr;
@@ -1074,22 +1115,34 @@ mspcg_status solve(mspcg_handle *h, mspcg_field *x, const mspcg_field *b, const 
     // One sweep with the Fletcher-Reeves beta: z is never stored; the direction
     // update p = z + beta p reads it from the block state (block_scatter_xpay)
     const bool fuse_p = pc && !s->flexible_beta && pc->n_sweeps <= 1;
-    auto update_p = [&](bool first) {  // p = z (first) or z + beta p
+    // x += alpha p waits for the direction update, which reads p anyway
+    bool x_pending = false;
+    auto update_p = [&](bool first) {  // p = z (first) or z + beta p, with the pending x += alpha p
       if (fuse_p) {
         tm.mark(PhaseTimer::PRECOND);
-        HIPCHK(block_scatter_xpay(pc->inner_prec, block_args(h, bg, nrhs), P, bg->x.v, bg->p.v,
-                                  bg->scal.as<double>(), scatter_mode(pc->n_inner, pc->inner_tol), w.rr,
-                                  (double)h->Vh * Ls * 24, w.beta, first ? 1 : 0, st));
+        HIPCHK(block_scatter_xpay(pc->inner_prec, block_args(h, bg, nrhs), P, x_pending ? xd : nullptr, bg->x.v,
+                                  bg->p.v, bg->scal.as<double>(), scatter_mode(pc->n_inner, pc->inner_tol), w.rr,
+                                  (double)h->Vh * Ls * 24, w.alpha, w.beta, first ? 1 : 0, st));
         tm.mark(PhaseTimer::BLAS);
       } else if (first) {
         HIPCHK(blas_axpby(pd, 1.0, zd, 0.0, zd, n, nrhs, st));
+      } else if (x_pending) {
+        HIPCHK(blas_update_xp(xd, pd, zd, w.alpha, w.beta, n, nrhs, st));
       } else {
         HIPCHK(blas_xpay(pd, zd, w.beta, n, nrhs, st));
       }
+      x_pending = false;
     };
+    auto finish_x = [&] {
+      if (x_pending) HIPCHK(blas_axpy(xd, pd, w.alpha, n, nrhs, st));
+      x_pending = false;
+    };
+    bool first_precond = true;
     auto precond = [&] {  // z = M^{-1} r and rho_new = <z, r> into w.tmp
       if (!pc) {
-        HIPCHK(hipMemcpyAsync(w.tmp, w.rr, nrhs * sizeof(double), hipMemcpyDeviceToDevice, st));
+        if (first_precond || s->flexible_beta)
+          HIPCHK(hipMemcpyAsync(w.tmp, w.rr, nrhs * sizeof(double), hipMemcpyDeviceToDevice, st));
+        first_precond = false;
         return;
       }
       tm.mark(PhaseTimer::PRECOND);
@@ -1118,41 +1171,120 @@ mspcg_status solve(mspcg_handle *h, mspcg_field *x, const mspcg_field *b, const 
     long long inner = 0;
     bool any = false;
     for (int a : active) any |= (a != 0);
+    // waits until the device has written the |r|^2 of the iteration with this tag
+    auto wait_rr = [&](int slot, int tag) {
+      long spins = 0;
+      for (int i = 0; i < nrhs; ++i) {
+        while (__atomic_load_n(&h->slots->tag[slot][i], __ATOMIC_ACQUIRE) != tag) {
+          __builtin_ia32_pause();
+          if (++spins % 4096 != 0) continue;
+          const hipError_t e = hipStreamQuery(st);
+          (void)hipGetLastError();  // (not ready is no error of a later launch)
+          if (e == hipErrorNotReady) continue;
+          HIPCHK(e);
+          if (__atomic_load_n(&h->slots->tag[slot][i], __ATOMIC_ACQUIRE) != tag)
+            fail(MSPCG_EHIP, "internal: the stream is idle and an iteration's residual was not reported");
+        }
+        hr[i] = h->slots->rr[slot][i];
+        if (!std::isfinite(hr[i])) fail(MSPCG_ENONFINITE, "non-finite value in a solver reduction");
+      }
+    };
+    // Far from convergence plain CG's host looks at an iteration's |r|^2 only
+    // after it has enqueued the next iteration, so the device never waits for
+    // it (an outer iteration of MSPCG is hundreds of times that wait).  Far:
+    // the last known |r| of every right-hand side is more than kFar times the
+    // largest reduction seen in one iteration above its tolerance.  Should one
+    // fall further, the solve stops one iteration later: x, r and p are those
+    // of that iteration.
+    constexpr double kFar = 10.0;
+    double drop = 0;  // largest |r_j|^2 / |r_{j+1}|^2 seen (0: none yet)
+    std::vector<double> hr_last;
+    auto see = [&](bool next) {  // after hr was filled; next: by the iteration after hr_last's
+      if (next)
+        for (int i = 0; i < nrhs; ++i)
+          if (active[i] && hr[i] > 0) drop = std::max(drop, hr_last[i] / hr[i]);
+      hr_last = hr;
+    };
+    auto is_far = [&] {
+      for (int i = 0; i < nrhs; ++i)
+        if (active[i] && !(hr[i] > kFar * kFar * std::max(1.0, drop) * tol2 * hb[i])) return false;
+      return drop > 0;
+    };
+    see(false);
     if (any) {
       precond();
       if (pc) inner += (long long)pc->n_inner * std::max(1, pc->n_sweeps);
       update_p(true);  // p = z
       HIPCHK(hipMemcpyAsync(w.rho, w.tmp, nrhs * sizeof(double), hipMemcpyDeviceToDevice, st));
+      int unseen = -1;  // the slot of the last iteration, if the host has not looked at it
       while (it < s->max_iter) {
+        const bool reliable = s->reliable_interval > 0 && (it + 1) % s->reliable_interval == 0;
+        const bool ahead =
+            !pc && !s->flexible_beta && !reliable && it + 1 < s->max_iter && !tm.on && h->verbose == 0 && is_far();
+        const int slot = it & 1, tag = ++h->next_tag;
+        ReduceOp pap_op, rr_op;
+        pap_op.mode = 1;
+        pap_op.active = rr_op.active = w.active;
+        pap_op.rho = rr_op.rho = w.rho;
+        pap_op.res = w.alpha;
+        rr_op.res = w.beta;
+        rr_op.host = h->slots->rr[slot];
+        rr_op.host_tag = h->slots->tag[slot];
+        rr_op.tag = tag;
+        if (ahead) rr_op.mode = 2;  // rho_new = |r|^2
         tm.mark(PhaseTimer::OP);
-        const int hop_parts = apply_mdagm(h, MSPCG_F64, nrhs, Q, P, h->tmp_o.v, h->tmp_e.v, part, st);
-        tm.mark(PhaseTimer::BLAS);
-        HIPCHK(blas_reduce(part, hop_parts, nrhs, w.pap, st));
-        HIPCHK(solver_scalars(0, nrhs, w.active, w.rho, w.pap, w.alpha, st));
-        HIPCHK(blas_update_xr(xd, rd, pd, qd, w.alpha, n, nrhs, part, st));
-        HIPCHK(blas_reduce(part, kBlasGrid, nrhs, w.rr, st));
+        if (s->flexible_beta) {  // keeps q = A p
+          const int hop_parts = apply_mdagm(h, MSPCG_F64, nrhs, Q, P, h->tmp_o.v, h->tmp_e.v, part, st);
+          tm.mark(PhaseTimer::BLAS);
+          HIPCHK(blas_reduce(part, hop_parts, nrhs, w.pap, st, pap_op));
+          HIPCHK(blas_update_xr(xd, rd, pd, qd, w.alpha, n, nrhs, part, st));
+          HIPCHK(blas_reduce(part, kBlasGrid, nrhs, w.rr, st, rr_op));
+        } else {
+          // <p, A p> = |D_PC p|^2 is summed by the second hop, so alpha is known
+          // before the third, and the fourth updates r in place with |r|^2: A p
+          // is never stored, and x waits for the update of p.  Vector passes of
+          // a CG iteration outside the hops' own: 11 -> 7 (FP64 16^3 x 32 x 16,
+          // with the host running ahead: 982 -> 804 us an iteration; 4^4 x 8,
+          // 11 -> 7 launches: 46 -> 25 us).
+          const Vec &to = h->tmp_o.v, &te = h->tmp_e.v;
+          global_hop(h, MSPCG_F64, nrhs, 1, to, P, 0, 1, EPI_M5INV, -0.5, &h->x1, nullptr, nullptr, nullptr, st);
+          const int parts2 = global_hop(h, MSPCG_F64, nrhs, 0, te, to, 0, 0, EPI_M5_OTHER, 0.5, nullptr, &P, part,
+                                        nullptr, st);
+          HIPCHK(blas_reduce(part, parts2, nrhs, w.pap, st, pap_op));
+          global_hop(h, MSPCG_F64, nrhs, 1, to, te, 1, 0, EPI_M5INV, -0.5, &h->x1, nullptr, nullptr, nullptr, st);
+          const int parts4 = global_update_hop(h, nrhs, R, Q, to, te, w.alpha, part, st);
+          tm.mark(PhaseTimer::BLAS);
+          HIPCHK(blas_reduce(part, parts4, nrhs, w.rr, st, rr_op));
+          x_pending = true;
+        }
         ++it;
-        to_host(w.rr, hr);
-        bool check = false;
-        for (int i = 0; i < nrhs; ++i) check |= active[i] && hr[i] <= tol2 * hb[i];
-        const bool reliable = s->reliable_interval > 0 && it % s->reliable_interval == 0;
-        if (check || reliable) {
-          true_residual();
-          bool changed = false;
-          for (int i = 0; i < nrhs; ++i)
-            if (active[i] && hr[i] <= tol2 * hb[i]) { active[i] = 0; changed = true; }
-          if (changed) push_active();
+        if (!ahead) {
+          wait_rr(slot, tag);
+          see(unseen < 0);
+          unseen = -1;
+          if (tm.on) HIPCHK(hipStreamSynchronize(st));
+          tm.drain();
+          bool check = false;
+          for (int i = 0; i < nrhs; ++i) check |= active[i] && hr[i] <= tol2 * hb[i];
+          if (check || reliable) {
+            finish_x();
+            true_residual();
+            bool changed = false;
+            for (int i = 0; i < nrhs; ++i)
+              if (active[i] && hr[i] <= tol2 * hb[i]) { active[i] = 0; changed = true; }
+            if (changed) push_active();
+          }
+          if (h->verbose > 0 && it % h->verbose == 0) {
+            double worst = 0;
+            for (int i = 0; i < nrhs; ++i)
+              if (hb[i] > 0) worst = std::max(worst, std::sqrt(hr[i] / hb[i]));
+            std::fprintf(stderr, "[mspcg] %s iteration %d: relative residual %.3e, %.1f s\n", pc ? "MSPCG" : "CG",
+                         it, worst, std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count());
+          }
+          any = false;
+          for (int a : active) any |= (a != 0);
+          if (!any) break;
         }
-        if (h->verbose > 0 && it % h->verbose == 0) {
-          double worst = 0;
-          for (int i = 0; i < nrhs; ++i)
-            if (hb[i] > 0) worst = std::max(worst, std::sqrt(hr[i] / hb[i]));
-          std::fprintf(stderr, "[mspcg] %s iteration %d: relative residual %.3e, %.1f s\n", pc ? "MSPCG" : "CG", it,
-                       worst, std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count());
-        }
-        any = false;
-        for (int a : active) any |= (a != 0);
-        if (!any) break;
         precond();
         if (pc) inner += (long long)pc->n_inner * std::max(1, pc->n_sweeps);
         if (s->flexible_beta) {
@@ -1161,11 +1293,19 @@ mspcg_status solve(mspcg_handle *h, mspcg_field *x, const mspcg_field *b, const 
           HIPCHK(blas_dot_partial(zd, qd, n, nrhs, part, st));
           HIPCHK(blas_reduce(part, kBlasGrid, nrhs, w.zq, st));
           HIPCHK(solver_scalars(2, nrhs, w.active, w.rho, w.tmp, w.beta, st, w.zq, w.pap));
-        } else {
-          HIPCHK(solver_scalars(1, nrhs, w.active, w.rho, w.tmp, w.beta, st));
+        } else if (rr_op.mode != 2) {
+          HIPCHK(solver_scalars(1, nrhs, w.active, w.rho, pc ? w.tmp : w.rr, w.beta, st));
         }
         update_p(false);
+        if (ahead) {
+          if (unseen >= 0) {
+            wait_rr(unseen, tag - 1);
+            see(true);
+          }
+          unseen = slot;
+        }
       }
+      finish_x();
     }
     // final true residual
     true_residual();

@@ -57,10 +57,11 @@ struct HopArgs {
   const void *mat;     // EPI_M5INV: chain coefficients of X (kChainHead + Ls values in the compute type)
   double mphi_b, mphi_c, mf, m5_alpha, m5_beta;
   double *partial;     // DOT: [gridDim.x][nrhs] partial sums of Re<w, out> (no w: |out|^2)
-  // Residual update fused into a block hop (upd_scal set): the value stored
-  // is out - alpha * hop result, out read first at the same site (in place),
-  // alpha = upd_scal[(upd_blk[site] nrhs + rhs) kScal + 1]; the DOT partials
-  // are then |stored value|^2.
+  // Residual update fused into the last hop of A or A_s (upd_scal set): the
+  // value stored is out - alpha * hop result, out read first at the same site
+  // (in place), alpha = upd_scal[rhs] on the full lattice and
+  // upd_scal[(upd_blk[site] nrhs + rhs) kScal + 1] on block domains; the DOT
+  // partials are then |stored value|^2.
   const double *upd_scal;
   const int *upd_blk;
   const void *dotw;
@@ -102,17 +103,34 @@ hipError_t launch_convert(const Vec &out, const Vec &in, int nrhs, long long nsi
 constexpr int kBlasWG = 256;
 constexpr int kBlasGrid = 512;  // workgroups per right-hand side (fixed: deterministic sums)
 hipError_t blas_dot_partial(const double *a, const double *b, long long n, int nrhs, double *partial, hipStream_t st);
-hipError_t blas_reduce(const double *partial, int nparts, int nrhs, double *out, hipStream_t st);
+// What a reduction forms from its sum v per right-hand side (device arrays
+// [nrhs]): mode 0 nothing more; 1: res = alpha = active ? rho / v : 0 (v = <p, A p>);
+// 2: res = beta = active ? v / rho : 0 and rho = v (v = rho_new).  With `host`
+// the sum also goes to host memory, followed by `tag` in host_tag.
+struct ReduceOp {
+  int mode = 0;
+  const int *active = nullptr;
+  double *rho = nullptr, *res = nullptr;
+  double *host = nullptr;
+  int *host_tag = nullptr;
+  int tag = 0;
+};
+hipError_t blas_reduce(const double *partial, int nparts, int nrhs, double *out, hipStream_t st,
+                       const ReduceOp &op = ReduceOp());
 // x += alpha p, r -= alpha q, partial |r|^2; alpha[r] read from scal
 hipError_t blas_update_xr(double *x, double *r, const double *p, const double *q, const double *alpha, long long n,
                           int nrhs, double *partial, hipStream_t st);
 // p = z + beta p
 hipError_t blas_xpay(double *p, const double *z, const double *beta, long long n, int nrhs, hipStream_t st);
+// x += alpha p, then p = z + beta p (alpha, beta: device arrays [nrhs])
+hipError_t blas_update_xp(double *x, double *p, const double *z, const double *alpha, const double *beta, long long n,
+                          int nrhs, hipStream_t st);
+// x += alpha p (alpha: device array [nrhs])
+hipError_t blas_axpy(double *x, const double *p, const double *alpha, long long n, int nrhs, hipStream_t st);
 // out = a x + b y (host scalars)
 hipError_t blas_axpby(double *out, double a, const double *x, double b, const double *y, long long n, int nrhs,
                       hipStream_t st);
 // Solver scalars per right-hand side (all device arrays [nrhs]):
-//   mode 0: alpha = active ? rho / pap : 0                       (x1 = pap)
 //   mode 1: beta = active ? rho_new / rho : 0; rho = rho_new     (x1 = rho_new; Fletcher-Reeves)
 //   mode 2: beta = active ? -zq / pap : 0; rho = rho_new         (x1 = rho_new, x2 = <z', A p>, x3 = <p, A p>;
 //           Polak-Ribiere, <z', r' - r> / <z, r> with r' - r = -alpha A p)
@@ -142,10 +160,11 @@ hipError_t block_scatter(int prec, const BlockArgs &b, const Vec &zglob, const V
                          double *partial, hipStream_t st);
 // p(cb) = v / scale + beta[rhs] p(cb) (first: p = v / scale), v as in
 // block_scatter: the outer direction update with the preconditioned residual
-// taken straight from the blocks (FP64 p)
-hipError_t block_scatter_xpay(int prec, const BlockArgs &b, const Vec &pglob, const Vec &xs, const Vec &ps,
-                              const double *scal, int mode, const double *rr, double n_total, const double *beta,
-                              int first, hipStream_t st);
+// taken straight from the blocks (FP64 p); xglob (optional, not with first):
+// x(cb) += alpha[rhs] p(cb) with the old p
+hipError_t block_scatter_xpay(int prec, const BlockArgs &b, const Vec &pglob, double *xglob, const Vec &xs,
+                              const Vec &ps, const double *scal, int mode, const double *rr, double n_total,
+                              const double *alpha, const double *beta, int first, hipStream_t st);
 // per (block, rhs): mode 0: alpha = rho/sum(partials) (0 if degenerate)
 //                   mode 1: rho_new = sum; beta = rho_new/rho (0 if rho = 0); rho = rho_new
 //                   mode 2: rho = sum (initialisation)

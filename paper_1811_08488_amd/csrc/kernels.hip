@@ -544,8 +544,9 @@ __global__ void __launch_bounds__(256, (HopWaves<S, XM>::value)) hop_kernel(cons
   const bool listed = site < a.nsites;
   const int row = listed ? site : 0;  // (inactive lanes compute on valid data and store nothing)
   const int cbr = listed ? a.site_cb[row] : -1;  // full lattice: cb; block domains: position of the site's links
-  const bool has_upd = !GLOBAL && a.upd_scal;
-  const int ublk = (has_upd && listed) ? a.upd_blk[row] : -1;
+  constexpr bool kUpd = EPI == EPI_M5DAG_MPHIDAG && DOT;  // variants that may update in place
+  const bool has_upd = kUpd && a.upd_scal;
+  const int ublk = (!GLOBAL && has_upd && listed) ? a.upd_blk[row] : -1;
   const bool active = lane_ok && (GLOBAL ? listed : cbr >= 0);
 
   // The eight neighbour indices are loaded once, with two 16-byte loads, and
@@ -587,13 +588,12 @@ __global__ void __launch_bounds__(256, (HopWaves<S, XM>::value)) hop_kernel(cons
 
   const int cb = GLOBAL ? cbr : 0;
   const int self = GLOBAL ? cb : site;  // index of this site in tables and outputs
-  // A fused CG residual update (block domains, upd_scal set) stores
-  // out - alpha (result): alpha is requested here, long before it is needed,
-  // and -alpha folds into the epilogue's coefficients (all linear in the
-  // result).
+  // A fused CG residual update (upd_scal set) stores out - alpha (result):
+  // alpha is requested here, long before it is needed, and -alpha folds into
+  // the epilogue's coefficients (all linear in the result).
   const bool upd = has_upd && active;
   double alpha_u = 0;
-  if (upd) alpha_u = a.upd_scal[((size_t)ublk * nrhs + r) * kScal + 1];
+  if (upd) alpha_u = a.upd_scal[GLOBAL ? (size_t)r : ((size_t)ublk * nrhs + r) * kScal + 1];
 
   int nbw[8];
   int outm = 0;
@@ -818,9 +818,12 @@ static hipError_t dispatch_hop(int dagger, int pre, int epi, int dot, int global
   MSPCG_HOP(1, 0, EPI_MPHIDAG, 0, 1)        // (M^4)^+ in
   MSPCG_HOP(0, 1, EPI_M5INV, 0, 1)          // M_phi M_5^-1 M^4 in (first hop of D_PC)
   MSPCG_HOP(0, 0, EPI_M5_OTHER, 0, 1)       // M_5 psi + 1/2 H c
+  if constexpr (std::is_same<S, double>::value) {
+    MSPCG_HOP(0, 0, EPI_M5_OTHER, 1, 1)     //   ... with the fused |out|^2 (<p, A p> = |D_PC p|^2; the FP64 solvers)
+  }
   MSPCG_HOP(1, 0, EPI_M5INV, 0, 1)          // M_5^-+ M_phi^+ (M^4)^+ y
   MSPCG_HOP(1, 0, EPI_M5DAG_MPHIDAG, 0, 1)  // M_5^+ y + 1/2 M_phi^+ H^+ f
-  MSPCG_HOP(1, 0, EPI_M5DAG_MPHIDAG, 1, 1)  //   ... with the fused <w, out>
+  MSPCG_HOP(1, 0, EPI_M5DAG_MPHIDAG, 1, 1)  //   ... with the fused <w, out>, or the residual update with its |r|^2
   MSPCG_HOP(0, 0, EPI_M5INV, 0, 0)          // the same four hops on block domains (M_phi p formed beforehand;
                                             // neighbours outside a domain enter with weight zero, which needs
                                             // the input unmixed: no M_phi on the input there)
@@ -987,16 +990,54 @@ hipError_t blas_dot_partial(const double *a, const double *b, long long n, int n
   return hipGetLastError();
 }
 
-// partial[p][r] -> out[r]; one workgroup per right-hand side
-__global__ void __launch_bounds__(kBlasWG) k_reduce(const double *partial, int nparts, int nrhs, double *out) {
+// partial[p][r] -> out[r], and what the solvers form from it; one workgroup per
+// right-hand side.  Bound by latency: each thread sums eight independent
+// strands (fixed order: deterministic).  4096 partials: 15 us with 256
+// threads and one strand each, 5 us so.
+constexpr int kReduceWG = 1024, kReduceStrands = 8;
+__global__ void __launch_bounds__(kReduceWG) k_reduce(const double *partial, int nparts, int nrhs, double *out,
+                                                      const ReduceOp op) {
+  __shared__ double sh[kReduceWG / 64];
   const int r = blockIdx.x;
-  double acc = 0;
-  for (int p = threadIdx.x; p < nparts; p += kBlasWG) acc += partial[(size_t)p * nrhs + r];
-  block_sum_store(acc, out + r);
+  double acc[kReduceStrands];
+#pragma unroll
+  for (int j = 0; j < kReduceStrands; ++j) acc[j] = 0;
+  for (int p0 = threadIdx.x; p0 < nparts; p0 += kReduceWG * kReduceStrands) {
+#pragma unroll
+    for (int j = 0; j < kReduceStrands; ++j) {
+      const int p = p0 + j * kReduceWG;
+      if (p < nparts) acc[j] += partial[(size_t)p * nrhs + r];
+    }
+  }
+#pragma unroll
+  for (int w = kReduceStrands / 2; w > 0; w >>= 1)
+#pragma unroll
+    for (int j = 0; j < w; ++j) acc[j] += acc[j + w];
+  double v = acc[0];
+#pragma unroll
+  for (int w = 32; w > 0; w >>= 1) v += __shfl_down(v, w, 64);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  v = 0;
+#pragma unroll
+  for (int w = 0; w < kReduceWG / 64; ++w) v += sh[w];
+  out[r] = v;
+  if (op.mode == 1) {  // v = <p, A p>
+    op.res[r] = (op.active[r] != 0 && v != 0.0) ? op.rho[r] / v : 0.0;
+  } else if (op.mode == 2) {  // v = rho_new
+    const bool on = op.active[r] != 0;
+    op.res[r] = (on && op.rho[r] != 0.0) ? v / op.rho[r] : 0.0;
+    if (on) op.rho[r] = v;
+  }
+  if (op.host) {  // the value, then its tag, in host memory
+    __hip_atomic_store(op.host + r, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(op.host_tag + r, op.tag, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
 }
 
-hipError_t blas_reduce(const double *partial, int nparts, int nrhs, double *out, hipStream_t st) {
-  hipLaunchKernelGGL(k_reduce, dim3(nrhs), dim3(kBlasWG), 0, st, partial, nparts, nrhs, out);
+hipError_t blas_reduce(const double *partial, int nparts, int nrhs, double *out, hipStream_t st, const ReduceOp &op) {
+  hipLaunchKernelGGL(k_reduce, dim3(nrhs), dim3(kReduceWG), 0, st, partial, nparts, nrhs, out, op);
   return hipGetLastError();
 }
 
@@ -1048,6 +1089,55 @@ hipError_t blas_xpay(double *p, const double *z, const double *beta, long long n
   return hipGetLastError();
 }
 
+// x += alpha p and p = z + beta p in one pass (the x update of an iteration
+// waits for beta: five passes over memory instead of the 3 + 3 of an update of
+// x and one of p).  Bound by memory.
+__global__ void __launch_bounds__(kBlasWG) k_update_xp(double *xv, double *pv, const double *zv, const double *alpha,
+                                                       const double *beta, long long n) {
+  const int r = blockIdx.y;
+  const double al = alpha[r], be = beta[r];
+  double2 *x = reinterpret_cast<double2 *>(xv + (size_t)r * n);
+  double2 *p = reinterpret_cast<double2 *>(pv + (size_t)r * n);
+  const double2 *z = reinterpret_cast<const double2 *>(zv + (size_t)r * n);
+  const long long n2 = n / 2;
+  for (long long i = (long long)blockIdx.x * kBlasWG + threadIdx.x; i < n2; i += (long long)kBlasGrid * kBlasWG) {
+    double2 xi = x[i], pi = p[i];
+    const double2 zi = z[i];
+    xi.x += al * pi.x;
+    xi.y += al * pi.y;
+    pi.x = zi.x + be * pi.x;
+    pi.y = zi.y + be * pi.y;
+    store16(x + i, xi);
+    store16(p + i, pi);
+  }
+}
+
+hipError_t blas_update_xp(double *x, double *p, const double *z, const double *alpha, const double *beta, long long n,
+                          int nrhs, hipStream_t st) {
+  hipLaunchKernelGGL(k_update_xp, dim3(kBlasGrid, nrhs), dim3(kBlasWG), 0, st, x, p, z, alpha, beta, n);
+  return hipGetLastError();
+}
+
+__global__ void __launch_bounds__(kBlasWG) k_axpy(double *xv, const double *pv, const double *alpha, long long n) {
+  const int r = blockIdx.y;
+  const double al = alpha[r];
+  double2 *x = reinterpret_cast<double2 *>(xv + (size_t)r * n);
+  const double2 *p = reinterpret_cast<const double2 *>(pv + (size_t)r * n);
+  const long long n2 = n / 2;
+  for (long long i = (long long)blockIdx.x * kBlasWG + threadIdx.x; i < n2; i += (long long)kBlasGrid * kBlasWG) {
+    double2 xi = x[i];
+    const double2 pi = p[i];
+    xi.x += al * pi.x;
+    xi.y += al * pi.y;
+    store16(x + i, xi);
+  }
+}
+
+hipError_t blas_axpy(double *x, const double *p, const double *alpha, long long n, int nrhs, hipStream_t st) {
+  hipLaunchKernelGGL(k_axpy, dim3(kBlasGrid, nrhs), dim3(kBlasWG), 0, st, x, p, alpha, n);
+  return hipGetLastError();
+}
+
 __global__ void __launch_bounds__(kBlasWG) k_axpby(double *ov, double a, const double *xv, double b, const double *yv,
                                                    long long n) {
   const int r = blockIdx.y;
@@ -1072,23 +1162,17 @@ __global__ void k_solver_scalars(int mode, int nrhs, const int *active, double *
   const int r = threadIdx.x;
   if (r >= nrhs) return;
   const bool on = active[r] != 0;
-  if (mode == 0) {
-    const double pap = x1[r];
-    out[r] = (on && pap != 0.0) ? rho[r] / pap : 0.0;
-  } else if (mode == 1) {
-    const double rn = x1[r];
+  const double rn = x1[r];
+  if (mode == 1)
     out[r] = (on && rho[r] != 0.0) ? rn / rho[r] : 0.0;
-    if (on) rho[r] = rn;
-  } else {
-    const double rn = x1[r], zq = x2[r], pap = x3[r];
-    out[r] = (on && pap != 0.0) ? -zq / pap : 0.0;
-    if (on) rho[r] = rn;
-  }
+  else
+    out[r] = (on && x3[r] != 0.0) ? -x2[r] / x3[r] : 0.0;
+  if (on) rho[r] = rn;
 }
 
 hipError_t solver_scalars(int mode, int nrhs, const int *active, double *rho, const double *x1, double *out,
                           hipStream_t st, const double *x2, const double *x3) {
-  if (mode == 2 && (!x2 || !x3)) return hipErrorInvalidValue;
+  if ((mode != 1 && mode != 2) || (mode == 2 && (!x2 || !x3))) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_solver_scalars, dim3(1), dim3(64), 0, st, mode, nrhs, active, rho, x1, out, x2, x3);
   return hipGetLastError();
 }
@@ -1183,11 +1267,13 @@ __global__ void __launch_bounds__(256) k_block_scatter(const BlockArgs b, double
 
 // The outer direction update fused with the scatter: p(cb) = v / scale +
 // beta p(cb) (first: p = v / scale) with v as in k_block_scatter, so the
-// preconditioned residual z is never stored.
+// preconditioned residual z is never stored.  With xg the outer solution's
+// pending update x += alpha p happens here too, where p is read anyway.
 template <typename S>
-__global__ void __launch_bounds__(256) k_block_scatter_xpay(const BlockArgs b, double *pg, long long pg_stride, Vec xs,
-                                                             Vec ps, const double *scal, int mode, const double *rr,
-                                                             double n_total, const double *beta, int first) {
+__global__ void __launch_bounds__(256) k_block_scatter_xpay(const BlockArgs b, double *pg, double *xg,
+                                                             long long pg_stride, Vec xs, Vec ps, const double *scal,
+                                                             int mode, const double *rr, double n_total,
+                                                             const double *alpha, const double *beta, int first) {
   using R = typename Traits<S>::R;
   const int tid = threadIdx.x, Ls = b.Ls, G = b.nrhs * Ls;
   const int sl = tid / G, rem = tid - sl * G, r = rem / Ls, s = rem - r * Ls;
@@ -1213,6 +1299,14 @@ __global__ void __launch_bounds__(256) k_block_scatter_xpay(const BlockArgs b, d
   } else {
     load24<double>(pg, nullptr, g, s, Ls, pn);
     const double be = beta[r];
+    if (xg) {
+      const double oal = alpha[r];
+      double x[24];
+      load24<double>(xg, nullptr, g, s, Ls, x);
+#pragma unroll
+      for (int k = 0; k < 24; ++k) x[k] = fma(oal, pn[k], x[k]);
+      store24<double>(xg, nullptr, g, s, Ls, x);
+    }
 #pragma unroll
     for (int k = 0; k < 24; ++k) pn[k] = fma(be, pn[k], inv * (double)v[k]);
   }
@@ -1386,13 +1480,13 @@ hipError_t block_scatter(int prec, const BlockArgs &b, const Vec &zglob, const V
   return hipGetLastError();
 }
 
-hipError_t block_scatter_xpay(int prec, const BlockArgs &b, const Vec &pglob, const Vec &xs, const Vec &ps,
-                              const double *scal, int mode, const double *rr, double n_total, const double *beta,
-                              int first, hipStream_t st) {
+hipError_t block_scatter_xpay(int prec, const BlockArgs &b, const Vec &pglob, double *xglob, const Vec &xs,
+                              const Vec &ps, const double *scal, int mode, const double *rr, double n_total,
+                              const double *alpha, const double *beta, int first, hipStream_t st) {
   if (pglob.prec != MSPCG_F64 || block_threads(b) > 256 || mode < 0 || mode > 2) return hipErrorInvalidValue;
   MSPCG_PREC_SWITCH(prec, hipLaunchKernelGGL(k_block_scatter_xpay<S>, dim3(block_grid(b)), dim3(block_threads(b)), 0,
-                                             st, b, (double *)pglob.data, pglob.stride, xs, ps, scal, mode, rr,
-                                             n_total, beta, first));
+                                             st, b, (double *)pglob.data, xglob, pglob.stride, xs, ps, scal, mode,
+                                             rr, n_total, alpha, beta, first));
   return hipGetLastError();
 }
 
