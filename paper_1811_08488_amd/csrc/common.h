@@ -576,4 +576,70 @@ __device__ inline void hop_half_h16(const half2_t h[6], const uint32_t *U, float
   }
 }
 
+// ---------------------------------------------------------------- FP16 link product on the matrix cores
+// v_mfma_f32_4x4x4_16b_f16 makes 16 independent 4x4 products, one per four
+// consecutive lanes: lane l holds row l % 4 of its group's A, its own column of
+// B, and receives its own column of A B (four rows in four registers).  With
+// Ls a multiple of 4 the four lanes of a group share a 4D site, so A is the
+// site's link and B the lanes' own half spinors: no value changes lanes, unlike
+// with the larger matrix instructions, whose fragments had to be transposed
+// through LDS (1.4-1.5 times slower than dot products).  A link is the real
+// 6 x 6 matrix of its three colour rows, rows 2a = (re U, -im U) and 2a + 1 =
+// (im U, re U) over (re h, im h) of the three colours, zero-padded to 8 columns:
+// rows 0-3 are one tile of four rows, rows 4 and 5 half of another.  Eight
+// instructions replace 36 dot products per direction, and two LDS reads of 16
+// bytes per lane five.  FP16 dslash_eo on 24^3 x 64 x 24: 510 -> 469 us.
+// (FP32 links on v_mfma_f32_4x4x1_16b_f32, 24 instructions for 72 multiply-adds,
+// were slower than the vector units: BF16 dslash_eo with 8 right-hand sides
+// 298 -> 313 us, FP32 A on 16^3 x 32 x 16 294 -> 300 us.)
+constexpr int kRowWords = 4;              // a row in LDS: 8 halves, two of them padding
+constexpr int kLinkWords = 6 * kRowWords;
+constexpr int kSiteWords = 8 * kLinkWords + 16;  // (16 more: the sites start on different LDS banks)
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
+
+// one colour row (three complex entries) of a stored link
+struct LinkRow { uint32_t w[3]; };
+__device__ inline LinkRow load_link_row(const _Float16 *p) {  // 12 bytes, 4-byte aligned
+  const uint32_t *q = reinterpret_cast<const uint32_t *>(p);
+  return LinkRow{{q[0], q[1], q[2]}};
+}
+// ... as the two rows it makes in LDS
+__device__ inline void stage_link_row(const LinkRow &r, uint32_t *o) {
+  const uint32_t *w = r.w;
+  reinterpret_cast<uint4 *>(o)[0] = make_uint4(w[0] ^ 0x80000000u, w[1] ^ 0x80000000u, w[2] ^ 0x80000000u, 0u);
+  reinterpret_cast<uint4 *>(o)[1] = make_uint4((w[0] >> 16) | (w[0] << 16), (w[1] >> 16) | (w[1] << 16),
+                                               (w[2] >> 16) | (w[2] << 16), 0u);
+}
+
+// hop_half_h16 on the matrix cores.  ra, rb: this lane's rows (lane % 4 and
+// 4 + lane % 2) of the link
+template <int MU, int SGN>
+__device__ inline void hop_half_mm(const half2_t h[6], const uint32_t *ra, const uint32_t *rb, float acc[24],
+                                   float n) {
+  const uint4 a = *reinterpret_cast<const uint4 *>(ra), b = *reinterpret_cast<const uint4 *>(rb);
+  const f16x4 a0 = __builtin_bit_cast(f16x4, make_uint2(a.x, a.y)), a1 = __builtin_bit_cast(f16x4, make_uint2(a.z, a.w));
+  const f16x4 b0 = __builtin_bit_cast(f16x4, make_uint2(b.x, b.y)), b1 = __builtin_bit_cast(f16x4, make_uint2(b.z, b.w));
+  f32x4 d[2], e[2];  // per spin: colours 0 and 1, colour 2
+  f16x4 lo[2], hi[2];
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    lo[k] = f16x4{h[3 * k].x, h[3 * k].y, h[3 * k + 1].x, h[3 * k + 1].y};
+    hi[k] = f16x4{h[3 * k + 2].x, h[3 * k + 2].y, (_Float16)0, (_Float16)0};
+  }
+  const f32x4 z = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int k = 0; k < 2; ++k) d[k] = __builtin_amdgcn_mfma_f32_4x4x4f16(a0, lo[k], z, 0, 0, 0);
+#pragma unroll
+  for (int k = 0; k < 2; ++k) e[k] = __builtin_amdgcn_mfma_f32_4x4x4f16(b0, lo[k], z, 0, 0, 0);
+#pragma unroll
+  for (int k = 0; k < 2; ++k) d[k] = __builtin_amdgcn_mfma_f32_4x4x4f16(a1, hi[k], d[k], 0, 0, 0);
+#pragma unroll
+  for (int k = 0; k < 2; ++k) e[k] = __builtin_amdgcn_mfma_f32_4x4x4f16(b1, hi[k], e[k], 0, 0, 0);
+  accumulate_colour<MU, SGN>(acc, 0, d[0][0], d[0][1], d[1][0], d[1][1], n);
+  accumulate_colour<MU, SGN>(acc, 1, d[0][2], d[0][3], d[1][2], d[1][3], n);
+  accumulate_colour<MU, SGN>(acc, 2, e[0][0], e[0][1], e[1][0], e[1][1], n);
+}
+
 }  // namespace mspcg

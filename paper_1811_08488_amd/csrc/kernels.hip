@@ -327,9 +327,12 @@ __device__ inline void hop_dir_norm(float *lds, int nthr, int tid, int s, int Ls
 // n(s)(X + Y)(s), cu n(s-1) X(s-1) and cl n(s+1) Y(s+1) are scaled by the
 // largest of their weights m, so that every coefficient is at most 1 and the
 // half-precision sum cannot overflow; m multiplies the link product.
-template <int MU, int SGN, int PRE, int XM>
+// U: the link as dot products read it; ra, rb: this lane's rows of it for the
+// matrix cores (MM).
+template <int MU, int SGN, int PRE, int XM, int MM>
 __device__ inline void hop_dir_h16(float *lds, int nthr, int tid, int s, int Ls, float cu, float cl,
-                                   const RawSite<_Float16> &raw, const uint32_t *U, float acc[24], bool out) {
+                                   const RawSite<_Float16> &raw, const uint32_t *U, const uint32_t *ra,
+                                   const uint32_t *rb, float acc[24], bool out) {
   uint32_t wd[12];
 #pragma unroll
   for (int i = 0; i < 12; ++i) wd[i] = raw.word(i);
@@ -355,7 +358,8 @@ __device__ inline void hop_dir_h16(float *lds, int nthr, int tid, int s, int Ls,
 #pragma unroll
     for (int k = 0; k < 6; ++k) h[k] = X[k] + Y[k];
   }
-  hop_half_h16<MU, SGN>(h, U, acc, m);
+  if constexpr (MM) hop_half_mm<MU, SGN>(h, ra, rb, acc, m);
+  else hop_half_h16<MU, SGN>(h, U, acc, m);
 }
 
 // ---------------------------------------------------------------- M_5^{-1} along the fifth dimension
@@ -502,13 +506,20 @@ __device__ inline void wg_partial(double *ldsd, int nthr, int tid, int Ls, int n
 // neighbour tables and links by the position in the list.  Otherwise (block
 // domains) all but the links are indexed by the position in the list, and
 // neighbours outside the domain enter with weight zero.
+// 4-byte words of LDS for the links of one site
+template <typename S, int MM>
+__host__ __device__ constexpr int hop_link_words() {
+  return MM ? kSiteWords : 144 * (int)sizeof(typename Traits<S>::R) / 4;
+}
+constexpr size_t kMaxLds = 160 * 1024;  // of a workgroup
+
 // Occupancy the register allocation of the hop kernel is held to (waves per SIMD).
 // (the LDS exchange keeps more values live; FP64 doubles every register)
 template <typename S, int XM> struct HopWaves { static constexpr int value = XM == kXLds ? 3 : 4; };
 template <int XM> struct HopWaves<double, XM> { static constexpr int value = 2; };
 template <int XM> struct HopWaves<float, XM> { static constexpr int value = 3; };  // (FP32 spinors: 4 would spill)
 
-template <typename S, int DAG, int PRE, int EPI, int DOT, int GLOBAL, int XM>
+template <typename S, int DAG, int PRE, int EPI, int DOT, int GLOBAL, int XM, int MM>
 __global__ void __launch_bounds__(256, (HopWaves<S, XM>::value)) hop_kernel(const HopArgs a) {
   using R = typename Traits<S>::R;
   extern __shared__ __align__(16) unsigned char smem[];
@@ -531,8 +542,12 @@ __global__ void __launch_bounds__(256, (HopWaves<S, XM>::value)) hop_kernel(cons
     r = g % nrhs;
     sl = g / nrhs;
   }
-  R *Lk = reinterpret_cast<R *>(smem);  // [nsite_wg][8][18] links of this workgroup's sites
-  R *lds = Lk + nsw * 144;              // exchange rows [nthr][kRow] (LDS mode, M_5^{-1})
+  // links of this workgroup's sites ([nsite_wg][8][18], or the rows for the
+  // matrix cores), then exchange rows [nthr][kRow] (LDS mode, M_5^{-1})
+  constexpr int kSiteLinks = hop_link_words<S, MM>();
+  R *Lk = reinterpret_cast<R *>(smem);
+  uint32_t *Lw = reinterpret_cast<uint32_t *>(smem);
+  R *lds = reinterpret_cast<R *>(Lw + nsw * kSiteLinks);
   const int tile = xcd_tile(blockIdx.x, gridDim.x);
   const int site = tile * nsw + sl;
   // The chain of dependent loads before the first spinor bounds a launch that
@@ -558,29 +573,36 @@ __global__ void __launch_bounds__(256, (HopWaves<S, XM>::value)) hop_kernel(cons
   const int4 *nb4 = reinterpret_cast<const int4 *>(a.nbr + (size_t)row * 8);
   const int4 q0 = nb4[0], q1 = nb4[1];
 
-  // the links of all sites of the workgroup, staged once into LDS with
-  // 16-byte loads (every link is used by all Ls x nrhs lanes of its site); the
-  // lanes of a site stage that site's links.  The first kLinkBatch words of a
-  // lane are requested together (all of them for Ls x nrhs >= 8): loaded one
-  // after the other they were 3 to 9 memory latencies in a row (FP64, Ls = 24
-  // to 8).  With the independent index loads: FP64 dslash_eo on 8^4 x 8 11.7 ->
-  // 9.2 us, FP64 A on 24^3 x 64 x 24 7221 -> 6773 us.
+  // the links of all sites of the workgroup, staged once into LDS (every link
+  // is used by all Ls x nrhs lanes of its site); the lanes of a site stage that
+  // site's links, in 16-byte words or, for the matrix cores, in colour rows.
+  // The first kLinkBatch pieces of a lane are requested together (all of them
+  // for Ls x nrhs >= 8): loaded one after the other they were 3 to 9 memory
+  // latencies in a row (FP64, Ls = 24 to 8).  With the independent index loads:
+  // FP64 dslash_eo on 8^4 x 8 11.7 -> 9.2 us, FP64 A on 24^3 x 64 x 24 7221 ->
+  // 6773 us.
   constexpr bool kH16 = std::is_same<S, _Float16>::value;
   constexpr int per = 16 / sizeof(S);
-  constexpr int nchunk = 144 / per;
+  constexpr int nchunk = MM ? 24 : 144 / per;
   constexpr int kLinkBatch = (nchunk + 7) / 8;
+  using Piece = typename std::conditional<MM != 0, LinkRow, uint4>::type;
   const int lstep = Ls * nrhs, lfirst = s + Ls * r;
-  const uint4 *lsrc = reinterpret_cast<const uint4 *>(a.links) +
-                      (size_t)(GLOBAL ? row : (cbr >= 0 ? cbr : 0)) * nchunk;
-  uint4 lq[kLinkBatch];
+  const S *lsrc = reinterpret_cast<const S *>(a.links) + (size_t)(GLOBAL ? row : (cbr >= 0 ? cbr : 0)) * 144;
+  auto load_piece = [&](int c) {
+    if constexpr (MM) return load_link_row(lsrc + c * 6);
+    else return *reinterpret_cast<const uint4 *>(lsrc + c * per);
+  };
+  Piece lq[kLinkBatch];
   auto load_links = [&] {
 #pragma unroll
     for (int j = 0; j < kLinkBatch; ++j)
-      if (j * lstep < nchunk) lq[j] = lsrc[min(lfirst + j * lstep, nchunk - 1)];
+      if (j * lstep < nchunk) lq[j] = load_piece(min(lfirst + j * lstep, nchunk - 1));
   };
-  auto stage_links = [&](int c, uint4 q) {
-    if constexpr (kH16)  // F16: (A, B) pairs for the packed link product
-      link_pairs_h16(q, reinterpret_cast<uint32_t *>(Lk) + sl * 144 + c * 8);
+  auto stage_piece = [&](int c, const Piece &q) {
+    if constexpr (MM)  // piece c: colour row c % 3 of direction c / 3
+      stage_link_row(q, Lw + sl * kSiteLinks + c * 2 * kRowWords);
+    else if constexpr (kH16)  // F16: (A, B) pairs for the packed link product
+      link_pairs_h16(q, Lw + sl * 144 + c * 8);
     else
       widen16<R>(reinterpret_cast<const S *>(&q), Lk + sl * 144 + c * per);
   };
@@ -630,15 +652,17 @@ __global__ void __launch_bounds__(256, (HopWaves<S, XM>::value)) hop_kernel(cons
 #pragma unroll
     for (int j = 0; j < kLinkBatch; ++j) {
       const int c = lfirst + j * lstep;
-      if (c < nchunk) stage_links(c, lq[j]);
+      if (c < nchunk) stage_piece(c, lq[j]);
     }
-    for (int c = lfirst + kLinkBatch * lstep; c < nchunk; c += lstep) stage_links(c, lsrc[c]);
+    for (int c = lfirst + kLinkBatch * lstep; c < nchunk; c += lstep) stage_piece(c, load_piece(c));
   }
   __syncthreads();
 
   R acc[24];
   zero24(acc);
   const R *Lsite = Lk + sl * 144;
+  const uint32_t *Lra = Lw + sl * kSiteLinks + (tid & 3) * kRowWords;
+  const uint32_t *Lrb = Lw + sl * kSiteLinks + (4 + (tid & 1)) * kRowWords;
   // PRE: the input is M_phi in = b (1 + (c/b) P_chi) in; the factor b goes
   // into the final scale (handles are created only for b != 0)
   const R pc = PRE ? (R)(a.mphi_c / a.mphi_b) : R(0);
@@ -667,26 +691,27 @@ __global__ void __launch_bounds__(256, (HopWaves<S, XM>::value)) hop_kernel(cons
       if (kPrefetch && bw == 1) load_nbr(cur, nbw[2]);
       if (!kPrefetch && d > 0) load_nbr(cur, nbw[bw]);
       const R *U = Lsite + d * 18;
+      const uint32_t *ra = Lra + d * kLinkWords, *rb = Lrb + d * kLinkWords;
       // (1 - g_mu) for the forward hop of H and the backward hop of H^+
       constexpr int sp = (DAG != 0) ? -1 : 1;
       const int sg = bw ? -sp : sp;
       const bool out = !GLOBAL && ((outm >> d) & 1);
-#define MSPCG_DIR(M)                                                                                        \
-  if constexpr (kH16) {                                                                                     \
-    const RawSite<S> &raw = (bw == 0 || !kPrefetch) ? cur : nxt;                                           \
-    const uint32_t *Uw = reinterpret_cast<const uint32_t *>(U);                                            \
-    if (sg > 0) hop_dir_h16<M, 1, PRE, XM>(lds, nthr, tid, s, Ls, pcu, pcl, raw, Uw, acc, out);             \
-    else hop_dir_h16<M, -1, PRE, XM>(lds, nthr, tid, s, Ls, pcu, pcl, raw, Uw, acc, out);                   \
-  } else if constexpr (Traits<S>::kNorm) {                                                                  \
-    const RawSite<S> &raw = (bw == 0 || !kPrefetch) ? cur : nxt;                                           \
-    if (sg > 0) hop_dir_norm<M, 1, PRE, XM>(lds, nthr, tid, s, Ls, pcu, pcl, one, raw, U, acc, out);        \
-    else hop_dir_norm<M, -1, PRE, XM>(lds, nthr, tid, s, Ls, pcu, pcl, one, raw, U, acc, out);              \
-  } else {                                                                                                  \
-    R v[24];                                                                                                \
-    if (bw == 0 || !kPrefetch) cur.decode(v); else nxt.decode(v);                                           \
-    const R wt = out ? R(0) : R(1);                                                                         \
-    if (sg > 0) hop_dir<M, 1, PRE, XM>(lds, nthr, tid, s, Ls, pcu, pcl, v, U, acc, wt);                     \
-    else hop_dir<M, -1, PRE, XM>(lds, nthr, tid, s, Ls, pcu, pcl, v, U, acc, wt);                           \
+#define MSPCG_DIR(M)                                                                                           \
+  if constexpr (kH16) {                                                                                        \
+    const RawSite<S> &raw = (bw == 0 || !kPrefetch) ? cur : nxt;                                               \
+    const uint32_t *Uw = reinterpret_cast<const uint32_t *>(U);                                                \
+    if (sg > 0) hop_dir_h16<M, 1, PRE, XM, MM>(lds, nthr, tid, s, Ls, pcu, pcl, raw, Uw, ra, rb, acc, out);    \
+    else hop_dir_h16<M, -1, PRE, XM, MM>(lds, nthr, tid, s, Ls, pcu, pcl, raw, Uw, ra, rb, acc, out);          \
+  } else if constexpr (Traits<S>::kNorm) {                                                                     \
+    const RawSite<S> &raw = (bw == 0 || !kPrefetch) ? cur : nxt;                                               \
+    if (sg > 0) hop_dir_norm<M, 1, PRE, XM>(lds, nthr, tid, s, Ls, pcu, pcl, one, raw, U, acc, out);\
+    else hop_dir_norm<M, -1, PRE, XM>(lds, nthr, tid, s, Ls, pcu, pcl, one, raw, U, acc, out);     \
+  } else {                                                                                                     \
+    R v[24];                                                                                                   \
+    if (bw == 0 || !kPrefetch) cur.decode(v); else nxt.decode(v);                                              \
+    const R wt = out ? R(0) : R(1);                                                                            \
+    if (sg > 0) hop_dir<M, 1, PRE, XM>(lds, nthr, tid, s, Ls, pcu, pcl, v, U, acc, wt);            \
+    else hop_dir<M, -1, PRE, XM>(lds, nthr, tid, s, Ls, pcu, pcl, v, U, acc, wt);                  \
   }
       switch (mu) {
         case 0: MSPCG_DIR(0) break;
@@ -781,26 +806,30 @@ __global__ void __launch_bounds__(256, (HopWaves<S, XM>::value)) hop_kernel(cons
 }
 
 template <typename S>
-static size_t hop_lds_bytes(const HopArgs &a, int nthr, int epi, int dot, int xm) {
+static size_t hop_lds_bytes(const HopArgs &a, int nthr, int epi, int dot, int xm, int mm) {
   using R = typename Traits<S>::R;
-  size_t b = (size_t)144 * a.nsite_wg * sizeof(R);
+  size_t b = (size_t)4 * (mm ? hop_link_words<S, 1>() : hop_link_words<S, 0>()) * a.nsite_wg;
   if (epi == EPI_M5INV || xm == kXLds) b += (size_t)kRow * nthr * sizeof(R);
   if (dot) b = std::max(b, (size_t)2 * nthr * sizeof(double));
   return b;
 }
 
-template <typename S, int DAG, int PRE, int EPI, int DOT, int GLOBAL>
+template <typename S, int DAG, int PRE, int EPI, int DOT, int GLOBAL, int MM>
 static hipError_t launch_hop_t(const HopArgs &a, hipStream_t st) {
   const int xm = xmode(a.Ls, a.nrhs);
   const int nthr = layout_threads(xm, a.Ls, a.nsite_wg * a.nrhs);
   const int grid = (a.nsites + a.nsite_wg - 1) / a.nsite_wg;
   if (a.nsite_wg < 1 || nthr > 256 || grid < 1) return hipErrorInvalidValue;
   const dim3 blk = (xm == kXLds) ? dim3(a.Ls, a.nrhs, a.nsite_wg) : dim3(nthr);
-  const size_t lds = hop_lds_bytes<S>(a, nthr, EPI, DOT, xm);
+  const size_t lds = hop_lds_bytes<S>(a, nthr, EPI, DOT, xm, MM);
+  if (lds > kMaxLds) return hipErrorInvalidValue;
   switch (xm) {
-    case kXDpp16: hipLaunchKernelGGL((hop_kernel<S, DAG, PRE, EPI, DOT, GLOBAL, kXDpp16>), dim3(grid), blk, lds, st, a); break;
-    case kXPerm: hipLaunchKernelGGL((hop_kernel<S, DAG, PRE, EPI, DOT, GLOBAL, kXPerm>), dim3(grid), blk, lds, st, a); break;
-    default: hipLaunchKernelGGL((hop_kernel<S, DAG, PRE, EPI, DOT, GLOBAL, kXLds>), dim3(grid), blk, lds, st, a); break;
+    case kXDpp16:  // (Ls = 16: F16 always on the matrix cores)
+      if constexpr (MM || !std::is_same<S, _Float16>::value)
+        hipLaunchKernelGGL((hop_kernel<S, DAG, PRE, EPI, DOT, GLOBAL, kXDpp16, MM>), dim3(grid), blk, lds, st, a);
+      break;
+    case kXPerm: hipLaunchKernelGGL((hop_kernel<S, DAG, PRE, EPI, DOT, GLOBAL, kXPerm, MM>), dim3(grid), blk, lds, st, a); break;
+    default: hipLaunchKernelGGL((hop_kernel<S, DAG, PRE, EPI, DOT, GLOBAL, kXLds, MM>), dim3(grid), blk, lds, st, a); break;
   }
   return hipGetLastError();
 }
@@ -810,10 +839,15 @@ int hop_groups_per_wave(int Ls, int nrhs) { return groups_per_wave(xmode(Ls, nrh
 
 template <typename S>
 static hipError_t dispatch_hop(int dagger, int pre, int epi, int dot, int global, const HopArgs &a, hipStream_t st) {
+  // F16 link products run on the matrix cores wherever the lanes of a site come
+  // in fours (every group of four lanes needs one link); other Ls take dot
+  // products.  Both sides on 24^3 x 64 x 24: 469 and 510 us a dslash_eo.
+  constexpr int kMM = std::is_same<S, _Float16>::value ? 1 : 0;
+  const bool mm = kMM && a.Ls % 4 == 0;
   // the combinations used by the operators (anything else is rejected)
 #define MSPCG_HOP(D, P, E, T, G)                                                \
   if (dagger == D && pre == P && epi == E && dot == T && (global != 0) == (G != 0)) \
-    return launch_hop_t<S, D, P, E, T, G>(a, st);
+    return mm ? launch_hop_t<S, D, P, E, T, G, kMM>(a, st) : launch_hop_t<S, D, P, E, T, G, 0>(a, st);
   MSPCG_HOP(0, 1, EPI_SCALE, 0, 1)          // M^4 in
   MSPCG_HOP(1, 0, EPI_MPHIDAG, 0, 1)        // (M^4)^+ in
   MSPCG_HOP(0, 1, EPI_M5INV, 0, 1)          // M_phi M_5^-1 M^4 in (first hop of D_PC)
