@@ -288,18 +288,8 @@ __device__ inline void exchange_pre_raw(float *lds, int nthr, int tid, int s, in
 template <int MU, int SGN, int PRE, int XM, typename S>
 __device__ inline void hop_dir_norm(float *lds, int nthr, int tid, int s, int Ls, float cu, float cl, float one,
                                     const RawSite<S> &raw, const float *U, float acc[24], bool out) {
-  // every direction widens its own copy of the stored words: shared by the
-  // eight direction variants, the widening would be hoisted out of them as
-  // separate conversions instead of folding into the multiply-adds
-  RawSite<S> rs = raw;
-#pragma unroll
-  for (int i = 0; i < 12; ++i) {
-    uint32_t x = rs.word(i);
-    asm volatile("" : "+v"(x));
-    rs.set_word(i, x);
-  }
   float v[24], X[12], Y[12], h[12];
-  rs.decode_raw(v);
+  raw.decode_raw(v);
   project_parts<MU, SGN>(v, X, Y);
   float n = out ? 0.f : raw.n;
   if (PRE) {
@@ -514,13 +504,12 @@ __host__ __device__ constexpr int hop_link_words() {
 constexpr size_t kMaxLds = 160 * 1024;  // of a workgroup
 
 // Occupancy the register allocation of the hop kernel is held to (waves per SIMD).
-// (the LDS exchange keeps more values live; FP64 doubles every register)
-template <typename S, int XM> struct HopWaves { static constexpr int value = XM == kXLds ? 3 : 4; };
-template <int XM> struct HopWaves<double, XM> { static constexpr int value = 2; };
-template <int XM> struct HopWaves<float, XM> { static constexpr int value = 3; };  // (FP32 spinors: 4 would spill)
+template <typename S> struct HopWaves { static constexpr int value = 4; };
+template <> struct HopWaves<double> { static constexpr int value = 2; };
+template <> struct HopWaves<float> { static constexpr int value = 3; };
 
 template <typename S, int DAG, int PRE, int EPI, int DOT, int GLOBAL, int XM, int MM>
-__global__ void __launch_bounds__(256, (HopWaves<S, XM>::value)) hop_kernel(const HopArgs a) {
+__global__ void __launch_bounds__(256, (HopWaves<S>::value)) hop_kernel(const HopArgs a) {
   using R = typename Traits<S>::R;
   extern __shared__ __align__(16) unsigned char smem[];
   const int Ls = a.Ls, nrhs = a.nrhs, nsw = a.nsite_wg;
@@ -565,8 +554,8 @@ __global__ void __launch_bounds__(256, (HopWaves<S, XM>::value)) hop_kernel(cons
   const bool active = lane_ok && (GLOBAL ? listed : cbr >= 0);
 
   // The eight neighbour indices are loaded once, with two 16-byte loads, and
-  // kept in registers (rotated by two per direction pair below): no spinor
-  // load ever waits for an index load issued after an earlier spinor load.
+  // kept in registers: no spinor load ever waits for an index load issued after
+  // an earlier spinor load.
   // Block domains: a neighbour outside the domain is stored as -1 - n with n
   // an in-domain substitute whose data enters with weight zero (bit d of
   // outm).
@@ -636,16 +625,24 @@ __global__ void __launch_bounds__(256, (HopWaves<S, XM>::value)) hop_kernel(cons
   // neighbour n of this lane: chunk 0 at in_s + n * sstride, its chunks cstride
   // apart, its norm at nrm_s + n * Ls (one multiply-add per address)
   // (32 x 32 -> 64-bit products: one multiply-add each)
-  const S *in_s = in + chunk_index<S>(rin, s, Ls, 0);
+  const char *in_s = reinterpret_cast<const char *>(in + chunk_index<S>(rin, s, Ls, 0));
   const uint32_t cstride = (uint32_t)Ls * Chunk<S>::kReals;
-  const uint32_t sstride = cstride * Chunk<S>::kCount;
-  const float *nrm_s = Traits<S>::kNorm ? a.in_norm + rin * Ls + s : nullptr;
+  const uint32_t sstride = (uint32_t)Ls * 24 * sizeof(S);  // (bytes)
+  const char *nrm_s = reinterpret_cast<const char *>(Traits<S>::kNorm ? a.in_norm + rin * Ls + s : nullptr);
   auto load_nbr = [&](RawSite<S> &dst, int n) {
     const uint64_t un = (uint32_t)n;
-    dst.load_at(in_s + un * sstride, cstride, Traits<S>::kNorm ? nrm_s + un * (uint32_t)Ls : nullptr);
+    dst.load_at(reinterpret_cast<const S *>(in_s + un * sstride), cstride,
+                reinterpret_cast<const float *>(nrm_s + un * (uint32_t)(Ls * 4)));
   };
-  RawSite<S> cur, nxt;
-  load_nbr(cur, nbw[0]);
+  // Neighbour spinors in flight ahead of the direction being computed.  FP64 at
+  // two waves per SIMD has registers for one (none: A on 24^3 x 64 x 24 6745 us,
+  // one: 6244; two waves with two: 7058, one wave with one: 6211).  The others
+  // take two (block hops 1-4 on 24^3 x 64 x 24, F16: 2942 us with none, 2813 with
+  // one, 2718 with two, 2712 with three).
+  constexpr int kAhead = std::is_same<S, double>::value ? 1 : 2;
+  RawSite<S> buf[kAhead + 1];
+#pragma unroll
+  for (int d = 0; d < kAhead; ++d) load_nbr(buf[d], nbw[d]);
 
   if (!GLOBAL) load_links();
   if (lane_ok) {
@@ -671,59 +668,47 @@ __global__ void __launch_bounds__(256, (HopWaves<S, XM>::value)) hop_kernel(cons
   // an opaque 1 (BF16, see hop_dir_norm)
   float one = 1.f;
   asm volatile("" : "+s"(one));
-  // One direction is always in flight ahead of the one being computed: the
-  // forward neighbour of mu uses buffer `cur`, the backward one `nxt`.  The
-  // loop over mu stays rolled on purpose (unrolled, the compiler hoists all
-  // eight directions' loads and runs out of registers).
-  // FP64 spinors are large: there the register budget is spent on occupancy
-  // instead of the prefetch (each direction loads just before it is used).
-  constexpr bool kPrefetch = sizeof(R) != 8;
-  // (nbw[0], nbw[1]) always hold the indices of directions 2 mu, 2 mu + 1
-#pragma unroll 1
-  for (int mu = 0; mu < 4; ++mu) {
-    if (kPrefetch) load_nbr(nxt, nbw[1]);
-#pragma unroll
-    for (int bw = 0; bw < 2; ++bw) {
-      const int d = 2 * mu + bw;
-      // (unconditional: after the last pair nbw[2] is direction 6 again, a
-      // cached reload; a load skipped on one path would make the wait
-      // before the backward direction drain every load in flight)
-      if (kPrefetch && bw == 1) load_nbr(cur, nbw[2]);
-      if (!kPrefetch && d > 0) load_nbr(cur, nbw[bw]);
-      const R *U = Lsite + d * 18;
-      const uint32_t *ra = Lra + d * kLinkWords, *rb = Lrb + d * kLinkWords;
-      // (1 - g_mu) for the forward hop of H and the backward hop of H^+
-      constexpr int sp = (DAG != 0) ? -1 : 1;
-      const int sg = bw ? -sp : sp;
-      const bool out = !GLOBAL && ((outm >> d) & 1);
-#define MSPCG_DIR(M)                                                                                           \
-  if constexpr (kH16) {                                                                                        \
-    const RawSite<S> &raw = (bw == 0 || !kPrefetch) ? cur : nxt;                                               \
-    const uint32_t *Uw = reinterpret_cast<const uint32_t *>(U);                                                \
-    if (sg > 0) hop_dir_h16<M, 1, PRE, XM, MM>(lds, nthr, tid, s, Ls, pcu, pcl, raw, Uw, ra, rb, acc, out);    \
-    else hop_dir_h16<M, -1, PRE, XM, MM>(lds, nthr, tid, s, Ls, pcu, pcl, raw, Uw, ra, rb, acc, out);          \
-  } else if constexpr (Traits<S>::kNorm) {                                                                     \
-    const RawSite<S> &raw = (bw == 0 || !kPrefetch) ? cur : nxt;                                               \
-    if (sg > 0) hop_dir_norm<M, 1, PRE, XM>(lds, nthr, tid, s, Ls, pcu, pcl, one, raw, U, acc, out);\
-    else hop_dir_norm<M, -1, PRE, XM>(lds, nthr, tid, s, Ls, pcu, pcl, one, raw, U, acc, out);     \
-  } else {                                                                                                     \
-    R v[24];                                                                                                   \
-    if (bw == 0 || !kPrefetch) cur.decode(v); else nxt.decode(v);                                              \
-    const R wt = out ? R(0) : R(1);                                                                            \
-    if (sg > 0) hop_dir<M, 1, PRE, XM>(lds, nthr, tid, s, Ls, pcu, pcl, v, U, acc, wt);            \
-    else hop_dir<M, -1, PRE, XM>(lds, nthr, tid, s, Ls, pcu, pcl, v, U, acc, wt);                  \
-  }
-      switch (mu) {
-        case 0: MSPCG_DIR(0) break;
-        case 1: MSPCG_DIR(1) break;
-        case 2: MSPCG_DIR(2) break;
-        default: MSPCG_DIR(3) break;
-      }
-#undef MSPCG_DIR
+  // The eight directions are written out: as a loop over mu with a switch for
+  // the code of a direction, each wave issued about 100 moves, copies and
+  // address instructions more per mu, and the registers that they held left
+  // FP64 no room to load ahead.  The scheduling barriers keep one direction's
+  // registers from overlapping the next one's.  Loop -> written out with two
+  // spinors ahead (FP64 one), 24^3 x 64 x 24: F16 block hops 1-4 2937 -> 2718 us,
+  // F16 dslash_eo 469 -> 420, FP32 A 3129 -> 3030, FP64 A 6673 -> 6208.
+  auto direction = [&](auto dc) {
+    constexpr int d = decltype(dc)::value, mu = d >> 1;
+    // (1 - g_mu) for the forward hop of H and the backward hop of H^+
+    constexpr int sg = (DAG != 0) == ((d & 1) != 0) ? 1 : -1;
+    RawSite<S> &raw = buf[d % (kAhead + 1)];
+    if (d + kAhead < 8) load_nbr(buf[(d + kAhead) % (kAhead + 1)], nbw[d + kAhead < 8 ? d + kAhead : 0]);
+    __builtin_amdgcn_sched_barrier(0);
+    const R *U = Lsite + d * 18;
+    const uint32_t *ra = Lra + d * kLinkWords, *rb = Lrb + d * kLinkWords;
+    const bool out = !GLOBAL && ((outm >> d) & 1);
+    if constexpr (kH16) {
+      hop_dir_h16<mu, sg, PRE, XM, MM>(lds, nthr, tid, s, Ls, pcu, pcl, raw, Lw + sl * 144 + d * 18, ra, rb, acc, out);
+    } else if constexpr (Traits<S>::kNorm) {
+      hop_dir_norm<mu, sg, PRE, XM>(lds, nthr, tid, s, Ls, pcu, pcl, one, raw, U, acc, out);
+    } else {
+      R v[24];
+      raw.decode(v);
+      hop_dir<mu, sg, PRE, XM>(lds, nthr, tid, s, Ls, pcu, pcl, v, U, acc, out ? R(0) : R(1));
     }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  direction(std::integral_constant<int, 0>{});
+  direction(std::integral_constant<int, 1>{});
+  direction(std::integral_constant<int, 2>{});
+  direction(std::integral_constant<int, 3>{});
+  direction(std::integral_constant<int, 4>{});
+  direction(std::integral_constant<int, 5>{});
+  direction(std::integral_constant<int, 6>{});
+  direction(std::integral_constant<int, 7>{});
+  // (the sums exist from here on: without this the compiler moves the
+  // multiply-adds of all eight directions into the blocks of the epilogue that
+  // use them, and keeps every product alive until then)
 #pragma unroll
-    for (int k = 0; k < 6; ++k) nbw[k] = nbw[k + 2];
-  }
+  for (int k = 0; k < 24; ++k) asm volatile("" : "+v"(acc[k]));
 
   const R scale = (R)(PRE ? a.scale * a.mphi_b : a.scale);
   // (the opaque copy keeps the conversion, and so the wait for the load, here)
