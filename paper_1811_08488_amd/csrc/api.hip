@@ -1377,14 +1377,20 @@ mspcg_status mspcg_create(mspcg_handle **hp, const mspcg_dwf *p, const double *g
     // index maps
     const int *L = p->L;
     const int Lxh = L[0] / 2;
-    // output sites of the full-lattice hop are visited column by column: the
-    // lattice is cut into columns of 12x12x12 spatial sites (8 where 12 does
-    // not divide an extent, the full extent where neither does) running the
-    // whole time direction, and each column is swept along t.  Consecutive workgroups (one XCD each range, see the
-    // kernels' workgroup renumbering) then need only a few neighbouring time
-    // slices of one column at a time, which stay in that XCD's L2.
+    // Output sites of the full-lattice hop are visited column by column, each
+    // column running the whole time direction and swept along t.  Consecutive
+    // workgroups (one XCD each range, see the kernels' workgroup renumbering)
+    // then need only a few neighbouring time slices of one column at a time,
+    // which an XCD's L2 holds in part, and XCDs that sweep neighbouring columns
+    // side by side share the columns' faces in the memory-side cache.  A
+    // spatial extent from 16 to 32 is halved: eight columns, one per XCD.
+    // Larger extents are cut into 12 (8 where 12 does not divide them), smaller
+    // ones only if 12 or 8 divides them.  FP64 A in us, columns of L/2 against
+    // 12 or 8 or, where neither divides, the extent: 32^3 x 64 x 12 7538 and 7985,
+    // 20^3 x 32 x 16 1116 and 1339; 48^3 x 32 x 12 14608 (24^3) and 13574 (12^3).
     int cdim[3];
-    for (int mu = 0; mu < 3; ++mu) cdim[mu] = (L[mu] % 12 == 0) ? 12 : (L[mu] % 8 == 0) ? 8 : L[mu];
+    for (int mu = 0; mu < 3; ++mu)
+      cdim[mu] = (L[mu] >= 16 && L[mu] <= 32) ? L[mu] / 2 : (L[mu] % 12 == 0) ? 12 : (L[mu] % 8 == 0) ? 8 : L[mu];
     if (const char *e = std::getenv("MSPCG_SITE_TILE")) {  // "x,y,z": spatial extent of the sweep's columns
       int t[3];
       if (std::sscanf(e, "%d,%d,%d", &t[0], &t[1], &t[2]) == 3 && t[0] > 0 && t[1] > 0 && t[2] > 0 &&
