@@ -357,6 +357,8 @@ int run_hop(mspcg_handle *h, int list_kind, int prec, int dag, int pre, int epi,
       HIPCHK(hipEventCreate(&e0));
       HIPCHK(hipEventCreate(&e1));
       float best = 0;
+      // (one timed launch of a candidate is enough where it takes 20 us or more)
+      const int reps = (size_t)a.nsites * a.nrhs * a.Ls * 24 * prec_bytes(prec) >= (64u << 20) ? 1 : 3;
       for (int c : cands) {
         const int thr = hop_threads(a.Ls, a.nrhs, c);
         if (thr > 256 || (thr < 64 && hop_threads(a.Ls, a.nrhs, 2 * c) <= 256 && c < kPad)) continue;
@@ -366,7 +368,7 @@ int run_hop(mspcg_handle *h, int list_kind, int prec, int dag, int pre, int epi,
           continue;
         }
         HIPCHK(hipEventRecord(e0, st));
-        for (int rep = 0; rep < 3; ++rep) HIPCHK(launch_hop(prec, dag, pre, epi, dot, global, a, st));
+        for (int rep = 0; rep < reps; ++rep) HIPCHK(launch_hop(prec, dag, pre, epi, dot, global, a, st));
         HIPCHK(hipEventRecord(e1, st));
         HIPCHK(hipEventSynchronize(e1));
         float ms = 0;
@@ -1634,9 +1636,8 @@ mspcg_status dwf_prepare_rhs(mspcg_handle *h, mspcg_field *b, const mspcg_field 
     if (phi_e->nrhs != nrhs || phi_o->nrhs != nrhs) fail(MSPCG_EINVAL, "nrhs mismatch");
     hipStream_t st = S(stream);
     ensure_fp64_temps(h, nrhs);
-    const long long n = (long long)h->Vh * h->par.Ls * 24;
     const Vec to = h->tmp_o.v, te = h->tmp_e.v;
-    // t_o = M_5^{-1} phi_o
+    // t_o = M_phi M_5^{-1} phi_o
     Op5Args a;
     std::memset(&a, 0, sizeof(a));
     a.nsites = h->Vh;
@@ -1647,11 +1648,13 @@ mspcg_status dwf_prepare_rhs(mspcg_handle *h, mspcg_field *b, const mspcg_field 
     a.out = to.data;
     a.stride = h->Vh;
     a.inv = 1;
-    a.chain = h->m5inv.ptr(MSPCG_F64);
+    a.chain = h->x1.ptr(MSPCG_F64);
     HIPCHK(launch_op5(MSPCG_F64, a, st));
-    // te = M^4_eo t_o ; phihat = phi_e - te (into te)
-    global_hop(h, MSPCG_F64, nrhs, 0, te, to, 0, 1, EPI_SCALE, -0.5, nullptr, nullptr, nullptr, nullptr, st);
-    HIPCHK(blas_axpby((double *)te.data, 1.0, (const double *)phi_e->data, -1.0, (const double *)te.data, n, nrhs, st));
+    // phihat = phi_e - M^4_eo M_5^{-1} phi_o = phi_e + 1/2 H t_o (into te): the sum in the hop's epilogue, and
+    // M_phi where M_5^{-1} is (as passes of their own, with the same in dwf_reconstruct, the two calls took 884
+    // us on 16^3 x 32 x 16; so 675)
+    const Vec pe = vec_of(h, phi_e);
+    global_hop(h, MSPCG_F64, nrhs, 0, te, to, 0, 0, EPI_ADD_OTHER, 0.5, nullptr, &pe, nullptr, nullptr, st);
     // b = D_PC^+ phihat
     global_hop(h, MSPCG_F64, nrhs, 1, to, te, 1, 0, EPI_M5INV, -0.5, &h->x1, nullptr, nullptr, nullptr,
                st);
@@ -1674,25 +1677,19 @@ mspcg_status dwf_reconstruct(mspcg_handle *h, mspcg_field *psi_o, const mspcg_fi
     const int nrhs = psi_o->nrhs;
     if (psi_e->nrhs != nrhs || phi_o->nrhs != nrhs) fail(MSPCG_EINVAL, "nrhs mismatch");
     hipStream_t st = S(stream);
-    ensure_fp64_temps(h, nrhs);
-    const long long n = (long long)h->Vh * h->par.Ls * 24;
-    const Vec to = h->tmp_o.v;
-    // t = phi_o - M^4_oe psi_e ; psi_o = M_5^{-1} t
-    global_hop(h, MSPCG_F64, nrhs, 1, to, vec_of(h, psi_e), 0, 1, EPI_SCALE, -0.5, nullptr, nullptr, nullptr, nullptr,
-               st);
-    HIPCHK(blas_axpby((double *)to.data, 1.0, (const double *)phi_o->data, -1.0, (const double *)to.data, n, nrhs, st));
-    Op5Args a;
-    std::memset(&a, 0, sizeof(a));
-    a.nsites = h->Vh;
-    a.Ls = h->par.Ls;
-    a.nrhs = nrhs;
-    a.nsite_wg = pick_nsite(nrhs, h->par.Ls);
-    a.in = to.data;
-    a.out = psi_o->data;
-    a.stride = h->Vh;
-    a.inv = 1;
-    a.chain = h->m5inv.ptr(MSPCG_F64);
-    HIPCHK(launch_op5(MSPCG_F64, a, st));
+    // psi_o = M_5^{-1} (phi_o - M^4_oe psi_e) = M_5^{-1} (phi_o + 1/2 H M_phi psi_e) in one hop; a caller whose psi_o shares memory with an input gets
+    // it by way of a temporary (the hop reads neighbours, and its first launch is repeated to tune it)
+    const size_t bytes = (size_t)nrhs * h->Vh * h->par.Ls * 24 * sizeof(double);
+    auto shares = [&](const mspcg_field *f) {
+      const uintptr_t a = (uintptr_t)f->data, o = (uintptr_t)psi_o->data;
+      return a < o + bytes && o < a + bytes;
+    };
+    const bool shared = shares(psi_e) || shares(phi_o);
+    if (shared) ensure_fp64_temps(h, nrhs);
+    const Vec po = vec_of(h, phi_o);
+    global_hop(h, MSPCG_F64, nrhs, 1, shared ? h->tmp_o.v : vec_of(h, psi_o), vec_of(h, psi_e), 0, 1, EPI_M5INV_OTHER,
+               0.5, &h->m5inv, &po, nullptr, nullptr, st);
+    if (shared) HIPCHK(hipMemcpyAsync(psi_o->data, h->tmp_o.v.data, bytes, hipMemcpyDeviceToDevice, st));
     HIPCHK(hipStreamSynchronize(st));
   });
 }

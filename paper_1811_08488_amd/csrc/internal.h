@@ -23,6 +23,8 @@ enum Epi {
   EPI_MPHIDAG = 2,        // out = scale * M_phi^+ hop
   EPI_M5_OTHER = 3,       // out = M_5 other + scale * hop
   EPI_M5DAG_MPHIDAG = 4,  // out = M_5^+ other + scale * M_phi^+ hop
+  EPI_ADD_OTHER = 5,      // out = other + scale * hop
+  EPI_M5INV_OTHER = 6,    // out = X (other + scale * hop), X from its chain coefficients
 };
 
 // A field [rhs][site][chunk][s][16 bytes] over a list of `stride` sites.
@@ -49,12 +51,13 @@ struct HopArgs {
   long long out_stride;
   const void *links;   // [position in the full lattice's list][8][18] for the output parity; sign of the time
                        // boundary folded in
-  const void *other;   // EPI_M5_OTHER / EPI_M5DAG_MPHIDAG operand
+  const void *other;   // operand of the epilogues that have one
   const float *other_norm;
   long long other_stride;
   const int *other_idx;  // output list position -> index in `other`, -1 outside (zero); nullptr: identity
   double scale;
-  const void *mat;     // EPI_M5INV: chain coefficients of X (kChainHead + Ls values in the compute type)
+  const void *mat;     // EPI_M5INV, EPI_M5INV_OTHER: chain coefficients of X (kChainHead + Ls values in the
+                       // compute type)
   double mphi_b, mphi_c, mf, m5_alpha, m5_beta;
   double *partial;     // DOT: [gridDim.x][nrhs] partial sums of Re<w, out> (no w: |out|^2)
   // Residual update fused into the last hop of A or A_s (upd_scal set): the

@@ -723,6 +723,13 @@ __global__ void __launch_bounds__(256, (HopWaves<S>::value)) hop_kernel(const Ho
   } else if (EPI == EPI_SCALE) {
 #pragma unroll
     for (int k = 0; k < 24; ++k) acc[k] *= scale;
+  } else if (EPI == EPI_ADD_OTHER || EPI == EPI_M5INV_OTHER) {  // (full lattice)
+    StoredOperand<S> o;
+    o.load(reinterpret_cast<const S *>(a.other), a.other_norm, (size_t)r * a.other_stride + max(cb, 0), s, Ls);
+    const R ow = o.norm();
+#pragma unroll
+    for (int k = 0; k < 24; ++k) acc[k] = fma(o.val(k), ow, scale * acc[k]);
+    if (EPI == EPI_M5INV_OTHER) m5_chain<DAG, R>(lds, tid, s, Ls, G, reinterpret_cast<const R *>(a.mat), R(1), acc);
   }
   if (EPI == EPI_M5_OTHER || EPI == EPI_M5DAG_MPHIDAG) {
     // (outside the block domain the operand vanishes; those lanes load
@@ -794,7 +801,7 @@ template <typename S>
 static size_t hop_lds_bytes(const HopArgs &a, int nthr, int epi, int dot, int xm, int mm) {
   using R = typename Traits<S>::R;
   size_t b = (size_t)4 * (mm ? hop_link_words<S, 1>() : hop_link_words<S, 0>()) * a.nsite_wg;
-  if (epi == EPI_M5INV || xm == kXLds) b += (size_t)kRow * nthr * sizeof(R);
+  if (epi == EPI_M5INV || epi == EPI_M5INV_OTHER || xm == kXLds) b += (size_t)kRow * nthr * sizeof(R);
   if (dot) b = std::max(b, (size_t)2 * nthr * sizeof(double));
   return b;
 }
@@ -839,6 +846,8 @@ static hipError_t dispatch_hop(int dagger, int pre, int epi, int dot, int global
   MSPCG_HOP(0, 0, EPI_M5_OTHER, 0, 1)       // M_5 psi + 1/2 H c
   if constexpr (std::is_same<S, double>::value) {
     MSPCG_HOP(0, 0, EPI_M5_OTHER, 1, 1)     //   ... with the fused |out|^2 (<p, A p> = |D_PC p|^2; the FP64 solvers)
+    MSPCG_HOP(0, 0, EPI_ADD_OTHER, 0, 1)    // phi + 1/2 H c (source preparation)
+    MSPCG_HOP(0, 1, EPI_M5INV_OTHER, 0, 1)  // M_5^-1 (phi + 1/2 H M_phi in) (reconstruction)
   }
   MSPCG_HOP(1, 0, EPI_M5INV, 0, 1)          // M_5^-+ M_phi^+ (M^4)^+ y
   MSPCG_HOP(1, 0, EPI_M5DAG_MPHIDAG, 0, 1)  // M_5^+ y + 1/2 M_phi^+ H^+ f
