@@ -120,7 +120,10 @@ struct BlockGeom {
   std::vector<int> be_n, o1_n, e2_n;         // true counts
   std::vector<int> be_lex, o1_lex, e2_lex;   // lex per padded entry (-1 padding)
   DBuf d_be_cb, d_be_blk, d_be_nbr, d_be_e2, d_o1_nbr_be, d_o1_nbr_e2, d_e2_nbr, d_e2_be, d_be_off, d_e2_off;
-  DBuf d_be_lk, d_o1_lk, d_e2_lk;  // position of a site's links (-1: padding)
+  DBuf d_be_lk, d_o1_lk;  // position of a site's links (-1: padding)
+  // the first two hops visit O1 and E2 in an order of their own: index in the vector and position of the links of
+  // the visited site (their neighbour tables are in this order)
+  DBuf d_o1v_self, d_o1v_lk, d_e2v_self, d_e2v_lk;
   // work vectors (inner precision); `gen` changes whenever they are reallocated
   // or cleared for another layout, so that graphs captured on them are never replayed
   int vprec = -1, vnrhs = 0;
@@ -477,6 +480,7 @@ BlockGeom *get_blocks(mspcg_handle *h, const int nblk[4], int no_snake, hipStrea
   if (it != h->blocks.end()) return it->second.get();
   const int *L = h->par.L;
   const int depth = no_snake ? 0 : 2;  // halo of the extended domains
+  constexpr int kSides = 1 + 5 * 5 * 5 * 5;  // displacements from the block: -2 .. 2 along each axis
   for (int mu = 0; mu < 4; ++mu) {
     if (nblk[mu] < 1 || nblk[mu] > L[mu]) fail(MSPCG_EINVAL, "nblk out of range");
     if (nblk[mu] >= 2 && L[mu] / nblk[mu] + (L[mu] % nblk[mu] ? 1 : 0) + 2 * depth > L[mu])
@@ -488,7 +492,21 @@ BlockGeom *get_blocks(mspcg_handle *h, const int nblk[4], int no_snake, hipStrea
   bg->nb = nblk[0] * nblk[1] * nblk[2] * nblk[3];
   const int V = h->V;
   std::vector<int> e2_of_lex(V, -1), o1_of_lex(V, -1);  // per-block scratch maps
+  std::vector<int> o1_self, e2_self;  // visiting order of the first two hops
   std::vector<int> be_cb, be_blk, be_nbr, be_e2, be_lk, o1_nbr_be, o1_nbr_e2, o1_lk, e2_nbr, e2_be, e2_lk;
+  {
+    // room for the lists (each block's padded count is known only in the loop;
+    // small blocks, whose boxes are mostly corners beyond the halo, grow theirs)
+    size_t box = 0;
+    for (int b = 0; b < bg->nb; ++b) {
+      size_t n = 1;
+      for (int mu = 0; mu < 4; ++mu) n *= L[mu] / nblk[mu] + 1 + (nblk[mu] >= 2 ? 2 * depth : 0);
+      box += n / 2 + block_align(h->par.Ls);
+    }
+    box = std::min(box, (size_t)2 * V);
+    for (auto *t : {&o1_self, &e2_self, &be_cb, &be_blk, &be_e2, &be_lk, &o1_lk, &e2_be, &e2_lk}) t->reserve(box);
+    for (auto *t : {&be_nbr, &o1_nbr_be, &o1_nbr_e2, &e2_nbr}) t->reserve(8 * box);
+  }
   bg->be_off.push_back(0);
   bg->o1_off.push_back(0);
   bg->e2_off.push_back(0);
@@ -504,17 +522,37 @@ BlockGeom *get_blocks(mspcg_handle *h, const int nblk[4], int no_snake, hipStrea
       lo[mu] = nblk[mu] >= 2 ? -depth : 0;
       hi[mu] = nblk[mu] >= 2 ? size[mu] + depth : size[mu];
     }
+    // Order of visit of an extended domain by the hops whose input lies on the
+    // next smaller one: the sites up to the outermost layer in lex order, then
+    // that layer (distance `depth` from the block), the sites with the same
+    // displacement from the block together: they have one to three neighbours in
+    // the smaller domain, the same directions throughout a side, and a wave of
+    // them does these alone.  `side` is 0 up to the outermost layer, else a
+    // number of the displacement (a counting sort: lex order within a side).
+    // Appends `padded` positions, the first one `base`.
+    auto visit = [&](const std::vector<int> &side, int base, int padded, std::vector<int> &order) {
+      std::vector<int> at(kSides + 1, 0);
+      for (int k : side) ++at[k + 1];
+      for (int k = 0; k < kSides; ++k) at[k + 1] += at[k];
+      const size_t first = order.size();
+      order.resize(first + padded);
+      const int n = (int)side.size();
+      for (int i = 0; i < n; ++i) order[first + at[side[i]]++] = base + i;
+      for (int i = n; i < padded; ++i) order[first + i] = base + i;
+    };
     // enumerate the extended box in local lex order (x fastest)
     std::vector<int> loc_be, loc_o1, loc_e2;
-    std::vector<int> dist_e2;
+    std::vector<int> dist_e2, side_o1, side_e2;
     for (int ut = lo[3]; ut < hi[3]; ++ut)
       for (int uz = lo[2]; uz < hi[2]; ++uz)
         for (int uy = lo[1]; uy < hi[1]; ++uy)
           for (int ux = lo[0]; ux < hi[0]; ++ux) {
             const int u[4] = {ux, uy, uz, ut};
-            int dist = 0, c[4];
+            int dist = 0, side = 0, c[4];
             for (int mu = 0; mu < 4; ++mu) {
-              dist += std::max(0, std::max(-u[mu], u[mu] - (size[mu] - 1)));
+              const int away = u[mu] < 0 ? u[mu] : std::max(0, u[mu] - (size[mu] - 1));  // -depth .. depth
+              dist += std::abs(away);
+              side = side * 5 + away + 2;
               c[mu] = ((start[mu] + u[mu]) % L[mu] + L[mu]) % L[mu];
             }
             const int g = lex_of(c);
@@ -522,8 +560,12 @@ BlockGeom *get_blocks(mspcg_handle *h, const int nblk[4], int no_snake, hipStrea
             if (par == 0 && dist <= depth) {
               loc_e2.push_back(g);
               dist_e2.push_back(dist);
+              side_e2.push_back(depth > 0 && dist == depth ? 1 + side : 0);
             }
-            if (par == 1 && dist <= depth / 2) loc_o1.push_back(g);
+            if (par == 1 && dist <= depth / 2) {
+              loc_o1.push_back(g);
+              side_o1.push_back(depth > 0 && dist == depth / 2 ? 1 + side : 0);
+            }
             if (par == 0 && dist == 0) loc_be.push_back(g);
           }
     const int be0 = bg->be_off.back(), o10 = bg->o1_off.back(), e20 = bg->e2_off.back();
@@ -538,20 +580,23 @@ BlockGeom *get_blocks(mspcg_handle *h, const int nblk[4], int no_snake, hipStrea
       for (int i = 0; i < ne2; ++i)
         if (dist_e2[i] == 0) be_of_e2[i] = be0 + k++;
     }
-    auto nb_lex = [&](int g, int d) {
-      int c[4];
-      int t = g;
-      for (int mu = 0; mu < 4; ++mu) { c[mu] = t % L[mu]; t /= L[mu]; }
-      const int mu = d >> 1;
-      c[mu] = (c[mu] + ((d & 1) ? -1 : 1) + L[mu]) % L[mu];
-      return lex_of(c);
+    auto nbrs_lex = [&](int g, int out[8]) {
+      for (int mu = 0, t = g, stride = 1; mu < 4; ++mu) {
+        const int c = t % L[mu];
+        t /= L[mu];
+        out[2 * mu] = c + 1 < L[mu] ? g + stride : g - c * stride;
+        out[2 * mu + 1] = c > 0 ? g - stride : g + (L[mu] - 1) * stride;
+        stride *= L[mu];
+      }
     };
+    int nl[8];
     // E2 (even) -> O1 neighbours, map to B_e
     for (int i = 0; i < pe2; ++i) {
       if (i < ne2) {
         const int g = loc_e2[i];
         e2_lk.push_back(h->pos_of_cb[0][g >> 1]);
-        for (int d = 0; d < 8; ++d) e2_nbr.push_back(o1_of_lex[nb_lex(g, d)]);
+        nbrs_lex(g, nl);
+        for (int d = 0; d < 8; ++d) e2_nbr.push_back(o1_of_lex[nl[d]]);
         e2_be.push_back(be_of_e2[i]);
         bg->e2_lex.push_back(g);
       } else {
@@ -566,8 +611,9 @@ BlockGeom *get_blocks(mspcg_handle *h, const int nblk[4], int no_snake, hipStrea
       if (i < no1) {
         const int g = loc_o1[i];
         o1_lk.push_back(h->pos_of_cb[1][g >> 1]);
+        nbrs_lex(g, nl);
         for (int d = 0; d < 8; ++d) {
-          const int e = e2_of_lex[nb_lex(g, d)];
+          const int e = e2_of_lex[nl[d]];
           o1_nbr_e2.push_back(e);
           o1_nbr_be.push_back(e >= 0 ? be_of_e2[e - e20] : -1);
         }
@@ -604,6 +650,8 @@ BlockGeom *get_blocks(mspcg_handle *h, const int nblk[4], int no_snake, hipStrea
     }
     for (int i = 0; i < no1; ++i) o1_of_lex[loc_o1[i]] = -1;
     for (int i = 0; i < ne2; ++i) e2_of_lex[loc_e2[i]] = -1;
+    visit(side_o1, o10, po1, o1_self);
+    visit(side_e2, e20, pe2, e2_self);
     bg->be_n.push_back(nbe);
     bg->o1_n.push_back(no1);
     bg->e2_n.push_back(ne2);
@@ -632,6 +680,16 @@ BlockGeom *get_blocks(mspcg_handle *h, const int nblk[4], int no_snake, hipStrea
       }
     }
   };
+  auto permuted = [](const std::vector<int> &t, const std::vector<int> &order, int width) {
+    std::vector<int> out(t.size());
+    for (size_t i = 0; i < order.size(); ++i)
+      for (int d = 0; d < width; ++d) out[i * width + d] = t[(size_t)order[i] * width + d];
+    return out;
+  };
+  const std::vector<int> o1v_lk = permuted(o1_lk, o1_self, 1), e2v_lk = permuted(e2_lk, e2_self, 1);
+  o1_nbr_be = permuted(o1_nbr_be, o1_self, 8);
+  e2_nbr = permuted(e2_nbr, e2_self, 8);
+  e2_be = permuted(e2_be, e2_self, 1);
   encode_out(be_nbr, bg->o1_tot);
   encode_out(e2_nbr, bg->o1_tot);
   encode_out(o1_nbr_e2, bg->e2_tot);
@@ -651,7 +709,10 @@ BlockGeom *get_blocks(mspcg_handle *h, const int nblk[4], int no_snake, hipStrea
   upload(bg->d_e2_be, e2_be, st);
   upload(bg->d_be_lk, be_lk, st);
   upload(bg->d_o1_lk, o1_lk, st);
-  upload(bg->d_e2_lk, e2_lk, st);
+  upload(bg->d_o1v_self, o1_self, st);
+  upload(bg->d_o1v_lk, o1v_lk, st);
+  upload(bg->d_e2v_self, e2_self, st);
+  upload(bg->d_e2v_lk, e2v_lk, st);
   upload(bg->d_be_off, bg->be_off, st);
   upload(bg->d_e2_off, bg->e2_off, st);
   HIPCHK(hipStreamSynchronize(st));
@@ -744,15 +805,17 @@ HopArgs block_hop_args(mspcg_handle *h, int nrhs, int nsites, const int *site_lk
 int block_hop(mspcg_handle *h, BlockGeom *bg, int prec, int nrhs, int which, const Vec &in, const Vec &in_mp,
               const Vec &out, double *partial, hipStream_t st, const double *upd_scal = nullptr) {
   if (which == 1) {  // c = M_phi M_5^{-1} (-1/2 H M_phi in) on O1
-    HopArgs a1 = block_hop_args(h, nrhs, bg->o1_tot, bg->d_o1_lk.as<int>(), bg->d_o1_nbr_be.as<int>(), in_mp,
+    HopArgs a1 = block_hop_args(h, nrhs, bg->o1_tot, bg->d_o1v_lk.as<int>(), bg->d_o1_nbr_be.as<int>(), in_mp,
                                 bg->o1v.v, 1, prec);
+    a1.self = bg->d_o1v_self.as<int>();
     a1.scale = -0.5;
     a1.mat = h->x1.ptr(prec);
     return run_hop(h, 1, prec, 0, 0, EPI_M5INV, 0, 0, a1, st);
   }
   if (which == 2) {  // y = M_5 in + 1/2 H c on E2
-    HopArgs a2 = block_hop_args(h, nrhs, bg->e2_tot, bg->d_e2_lk.as<int>(), bg->d_e2_nbr.as<int>(), bg->o1v.v,
+    HopArgs a2 = block_hop_args(h, nrhs, bg->e2_tot, bg->d_e2v_lk.as<int>(), bg->d_e2_nbr.as<int>(), bg->o1v.v,
                                 bg->e2v.v, 0, prec);
+    a2.self = bg->d_e2v_self.as<int>();
     a2.scale = 0.5;
     a2.other = in.data;
     a2.other_norm = in.norm;

@@ -40,6 +40,7 @@ struct HopArgs {
   int Ls, nrhs, nsite_wg;
   const int *site_cb;  // [nsites] full lattice: cb of the output site; block domains: the position of its
                        // links in the full lattice's list (-1: padding)
+  const int *self;     // block domains: [nsites] index of the output site in its vector (nullptr: the list position)
   const int *nbr;      // [list position][8] input index of neighbour d = 2 mu + (0 fwd, 1 bwd); in block domains
                        // a neighbour outside the domain is stored as -1 - alt (alt: an input index whose data is
                        // loaded with weight 0)

@@ -598,7 +598,8 @@ __global__ void __launch_bounds__(256, (HopWaves<S>::value)) hop_kernel(const Ho
   if (GLOBAL) load_links();
 
   const int cb = GLOBAL ? cbr : 0;
-  const int self = GLOBAL ? cb : site;  // index of this site in tables and outputs
+  // index of this site in the output (and what is read at the same site)
+  const int self = GLOBAL ? cb : ((!DAG && a.self) ? a.self[row] : row);
   // A fused CG residual update (upd_scal set) stores out - alpha (result):
   // alpha is requested here, long before it is needed, and -alpha folds into
   // the epilogue's coefficients (all linear in the result).
@@ -620,6 +621,24 @@ __global__ void __launch_bounds__(256, (HopWaves<S>::value)) hop_kernel(const Ho
       }
     }
   }
+  // Directions that some site of the wave has inside the domain.  The halo
+  // sites of the first two block hops have one to three neighbours inside; they
+  // are visited together, by the side of the block they lie on, and a wave of
+  // them reads and computes its few directions only.  (Halo sites are 47% of
+  // O1 and 38% of E2 for blocks of 8^3 x 16.  Hops 1 and 2 of 16^3 x 32, all
+  // eight directions -> the live ones: FP32 Ls 16 261 -> 244 us, BF16 Ls 12
+  // with 8 sources 1295 -> 1227, F16 Ls 24 263 -> 260; three steps of the FP32
+  // block CG 1987 -> 1890.)  Four or more live directions keep the loads ahead.
+  constexpr bool kSparse = !GLOBAL && !DAG;
+  constexpr int kSparseMost = 3;
+  uint32_t live = 0;
+  if constexpr (kSparse) {
+#pragma unroll
+    for (int d = 0; d < 8; ++d)
+      if (__ballot(active && !((outm >> d) & 1)) != 0) live |= 1u << d;
+    live = __builtin_amdgcn_readfirstlane(live);
+  }
+  const bool sparse = kSparse && __builtin_popcount(live) <= kSparseMost;
   const S *in = reinterpret_cast<const S *>(a.in);
   const size_t rin = (size_t)r * a.in_stride;
   // neighbour n of this lane: chunk 0 at in_s + n * sstride, its chunks cstride
@@ -641,8 +660,10 @@ __global__ void __launch_bounds__(256, (HopWaves<S>::value)) hop_kernel(const Ho
   // one, 2718 with two, 2712 with three).
   constexpr int kAhead = std::is_same<S, double>::value ? 1 : 2;
   RawSite<S> buf[kAhead + 1];
+  if (!sparse) {
 #pragma unroll
-  for (int d = 0; d < kAhead; ++d) load_nbr(buf[d], nbw[d]);
+    for (int d = 0; d < kAhead; ++d) load_nbr(buf[d], nbw[d]);
+  }
 
   if (!GLOBAL) load_links();
   if (lane_ok) {
@@ -675,13 +696,17 @@ __global__ void __launch_bounds__(256, (HopWaves<S>::value)) hop_kernel(const Ho
   // registers from overlapping the next one's.  Loop -> written out with two
   // spinors ahead (FP64 one), 24^3 x 64 x 24: F16 block hops 1-4 2937 -> 2718 us,
   // F16 dslash_eo 469 -> 420, FP32 A 3129 -> 3030, FP64 A 6673 -> 6208.
-  auto direction = [&](auto dc) {
+  // (the sums exist from here on: without this the compiler moves the
+  // multiply-adds of all directions into the later blocks that use them, and
+  // keeps every product alive until then)
+  auto pin_sums = [&]() {
+#pragma unroll
+    for (int k = 0; k < 24; ++k) asm volatile("" : "+v"(acc[k]));
+  };
+  auto product = [&](auto dc, const RawSite<S> &raw) {
     constexpr int d = decltype(dc)::value, mu = d >> 1;
     // (1 - g_mu) for the forward hop of H and the backward hop of H^+
     constexpr int sg = (DAG != 0) == ((d & 1) != 0) ? 1 : -1;
-    RawSite<S> &raw = buf[d % (kAhead + 1)];
-    if (d + kAhead < 8) load_nbr(buf[(d + kAhead) % (kAhead + 1)], nbw[d + kAhead < 8 ? d + kAhead : 0]);
-    __builtin_amdgcn_sched_barrier(0);
     const R *U = Lsite + d * 18;
     const uint32_t *ra = Lra + d * kLinkWords, *rb = Lrb + d * kLinkWords;
     const bool out = !GLOBAL && ((outm >> d) & 1);
@@ -694,21 +719,39 @@ __global__ void __launch_bounds__(256, (HopWaves<S>::value)) hop_kernel(const Ho
       raw.decode(v);
       hop_dir<mu, sg, PRE, XM>(lds, nthr, tid, s, Ls, pcu, pcl, v, U, acc, out ? R(0) : R(1));
     }
+  };
+  auto direction = [&](auto dc) {
+    constexpr int d = decltype(dc)::value;
+    if (d + kAhead < 8) load_nbr(buf[(d + kAhead) % (kAhead + 1)], nbw[d + kAhead < 8 ? d + kAhead : 0]);
+    __builtin_amdgcn_sched_barrier(0);
+    product(dc, buf[d % (kAhead + 1)]);
     __builtin_amdgcn_sched_barrier(0);
   };
-  direction(std::integral_constant<int, 0>{});
-  direction(std::integral_constant<int, 1>{});
-  direction(std::integral_constant<int, 2>{});
-  direction(std::integral_constant<int, 3>{});
-  direction(std::integral_constant<int, 4>{});
-  direction(std::integral_constant<int, 5>{});
-  direction(std::integral_constant<int, 6>{});
-  direction(std::integral_constant<int, 7>{});
-  // (the sums exist from here on: without this the compiler moves the
-  // multiply-adds of all eight directions into the blocks of the epilogue that
-  // use them, and keeps every product alive until then)
-#pragma unroll
-  for (int k = 0; k < 24; ++k) asm volatile("" : "+v"(acc[k]));
+  auto sparse_direction = [&](auto dc) {
+    constexpr int d = decltype(dc)::value;
+    if (!((live >> d) & 1)) return;
+    RawSite<S> raw;
+    load_nbr(raw, nbw[d]);
+    product(dc, raw);
+    pin_sums();
+  };
+  auto all = [](auto &&f) {
+    f(std::integral_constant<int, 0>{});
+    f(std::integral_constant<int, 1>{});
+    f(std::integral_constant<int, 2>{});
+    f(std::integral_constant<int, 3>{});
+    f(std::integral_constant<int, 4>{});
+    f(std::integral_constant<int, 5>{});
+    f(std::integral_constant<int, 6>{});
+    f(std::integral_constant<int, 7>{});
+  };
+  if constexpr (kSparse) {
+    if (sparse) all(sparse_direction);
+    else all(direction);
+  } else {
+    all(direction);
+  }
+  pin_sums();
 
   const R scale = (R)(PRE ? a.scale * a.mphi_b : a.scale);
   // (the opaque copy keeps the conversion, and so the wait for the load, here)
