@@ -120,8 +120,8 @@ __device__ inline void load24(const bf16 *base, const float *norm, size_t site4,
 // that stays in L2 only displaces inputs that neighbouring sites still need.
 // With ordinary -> with these stores: FP32 A on 16^3 x 32 x 16 309 -> 298 us,
 // FP64 CG there 304 -> 296 ms, block CG FP32 k = 6 4249 -> 4109 us, MSPCG F16
-// k = 8 at Ls = 24 828 -> 801 ms; the BF16 hop, bound by vector issue, lost 0.6%
-// and keeps ordinary stores.
+// k = 8 at Ls = 24 828 -> 801 ms; the BF16 hop, then bound by vector issue, lost
+// 0.6% and keeps ordinary stores.
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 template <typename T>
 __device__ inline void store16(void *p, const T &v) {
@@ -601,7 +601,8 @@ typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 
 // one colour row (three complex entries) of a stored link
 struct LinkRow { uint32_t w[3]; };
-__device__ inline LinkRow load_link_row(const _Float16 *p) {  // 12 bytes, 4-byte aligned
+template <typename S> __device__ inline LinkRow load_link_row(const S *p) {  // 12 bytes, 4-byte aligned
+  static_assert(sizeof(S) == 2, "two reals in a word");
   const uint32_t *q = reinterpret_cast<const uint32_t *>(p);
   return LinkRow{{q[0], q[1], q[2]}};
 }
@@ -637,6 +638,63 @@ __device__ inline void hop_half_mm(const half2_t h[6], const uint32_t *ra, const
   for (int k = 0; k < 2; ++k) d[k] = __builtin_amdgcn_mfma_f32_4x4x4f16(a1, hi[k], d[k], 0, 0, 0);
 #pragma unroll
   for (int k = 0; k < 2; ++k) e[k] = __builtin_amdgcn_mfma_f32_4x4x4f16(b1, hi[k], e[k], 0, 0, 0);
+  accumulate_colour<MU, SGN>(acc, 0, d[0][0], d[0][1], d[1][0], d[1][1], n);
+  accumulate_colour<MU, SGN>(acc, 1, d[0][2], d[0][3], d[1][2], d[1][3], n);
+  accumulate_colour<MU, SGN>(acc, 2, e[0][0], e[0][1], e[1][0], e[1][1], n);
+}
+
+// BF16 spinors without M_phi on the input: a projected half spinor is X + Y, two
+// stored values in each component, so U h = [U | U] (X, Y) is taken on the stored
+// words themselves, 12 columns of them in three instructions without padding:
+// nothing is widened, added or rounded on the way (exact products, FP32 sums).
+// The links are BF16 numbers as they are stored.  A direction takes 12 matrix
+// instructions and about 40 others; widening, projecting and 72 multiply-adds
+// took 170.  Daggered dslash_eo, FP32 arithmetic -> this: 16^3 x 32, Ls 16 44.6
+// -> 41.7 us, Ls 24 63.9 -> 59.7, 8^4 x 8 5.7 -> 4.9, eight sources of Ls 12
+// 283 -> 280 (bound by memory traffic now, as F16: 282).  With M_phi on the
+// input the FP32 path stays: the mixed values are no stored ones.
+// ra, rb: as in hop_half_mm
+template <int SGN> __device__ inline uint32_t times_i_b16(uint32_t w) {  // SGN i z of (re, im) in (low, high)
+  return ((w >> 16) | (w << 16)) ^ (SGN > 0 ? 0x00008000u : 0x80000000u);
+}
+template <int SGN> __device__ inline uint32_t sgn_b16(uint32_t w) { return SGN > 0 ? w : w ^ 0x80008000u; }
+
+template <int MU, int SGN>
+__device__ inline void hop_dir_b16_mm(const RawSite<bf16> &raw, const uint32_t *ra, const uint32_t *rb, float acc[24],
+                                      float n) {
+  typedef short b16x4 __attribute__((ext_vector_type(4)));
+  auto pair = [](uint32_t x, uint32_t y) { return __builtin_bit_cast(b16x4, make_uint2(x, y)); };
+  const uint4 a = *reinterpret_cast<const uint4 *>(ra), b = *reinterpret_cast<const uint4 *>(rb);
+  uint32_t w[12], Y[6];  // Y = -SGN B l, as in project_parts
+#pragma unroll
+  for (int i = 0; i < 12; ++i) {
+    w[i] = raw.word(i);
+    // (each word a value of its own: otherwise pairs of words that straddle the
+    // loaded ones are read as vectors, through scratch memory)
+    asm("" : "+v"(w[i]));
+  }
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    const uint32_t l0 = w[6 + c], l1 = w[9 + c];
+    if (MU == 0) {
+      Y[c] = times_i_b16<SGN>(l1); Y[3 + c] = times_i_b16<SGN>(l0);
+    } else if (MU == 1) {
+      Y[c] = sgn_b16<SGN>(l1); Y[3 + c] = sgn_b16<-SGN>(l0);
+    } else if (MU == 2) {
+      Y[c] = times_i_b16<SGN>(l0); Y[3 + c] = times_i_b16<-SGN>(l1);
+    } else {
+      Y[c] = sgn_b16<-SGN>(l0); Y[3 + c] = sgn_b16<-SGN>(l1);
+    }
+  }
+  f32x4 d[2], e[2];  // per spin: colours 0 and 1, colour 2
+  const f32x4 z = {0.f, 0.f, 0.f, 0.f};
+  auto mm = [](b16x4 u, b16x4 h, f32x4 c) { return __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(u, h, c, 0, 0, 0); };
+  const b16x4 a0 = pair(a.x, a.y), b0 = pair(b.x, b.y), h0 = pair(w[0], w[1]), g0 = pair(w[3], w[4]);
+  d[0] = mm(a0, h0, z), d[1] = mm(a0, g0, z), e[0] = mm(b0, h0, z), e[1] = mm(b0, g0, z);
+  const b16x4 a1 = pair(a.z, a.x), b1 = pair(b.z, b.x), h1 = pair(w[2], Y[0]), g1 = pair(w[5], Y[3]);
+  d[0] = mm(a1, h1, d[0]), d[1] = mm(a1, g1, d[1]), e[0] = mm(b1, h1, e[0]), e[1] = mm(b1, g1, e[1]);
+  const b16x4 a2 = pair(a.y, a.z), b2 = pair(b.y, b.z), h2 = pair(Y[1], Y[2]), g2 = pair(Y[4], Y[5]);
+  d[0] = mm(a2, h2, d[0]), d[1] = mm(a2, g2, d[1]), e[0] = mm(b2, h2, e[0]), e[1] = mm(b2, g2, e[1]);
   accumulate_colour<MU, SGN>(acc, 0, d[0][0], d[0][1], d[1][0], d[1][1], n);
   accumulate_colour<MU, SGN>(acc, 1, d[0][2], d[0][3], d[1][2], d[1][3], n);
   accumulate_colour<MU, SGN>(acc, 2, e[0][0], e[0][1], e[1][0], e[1][1], n);

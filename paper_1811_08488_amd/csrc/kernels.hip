@@ -283,7 +283,8 @@ __device__ inline void exchange_pre_raw(float *lds, int nthr, int tid, int s, in
 // projection works on the stored values (widened to FP32) and n multiplies
 // the link product as it is accumulated.  With M_phi on the input the
 // neighbours' norms enter the mixing coefficients as n(s -+ 1)/n(s) (a zero
-// site has no stored values and uses n = 1).  `one` is an opaque 1 that keeps
+// site has no stored values and uses n = 1).  Taken with M_phi on the input and
+// for Ls that are no multiple of four (otherwise hop_dir_b16_mm).  `one` is an opaque 1 that keeps
 // each sum a multiply-add.
 template <int MU, int SGN, int PRE, int XM, typename S>
 __device__ inline void hop_dir_norm(float *lds, int nthr, int tid, int s, int Ls, float cu, float cl, float one,
@@ -494,8 +495,9 @@ __device__ inline void wg_partial(double *ldsd, int nthr, int tid, int Ls, int n
 // GLOBAL: the output list is the whole parity (site_cb a permutation of cb in
 // column-sweep order); outputs and the `other`/dot operands are indexed by cb,
 // neighbour tables and links by the position in the list.  Otherwise (block
-// domains) all but the links are indexed by the position in the list, and
-// neighbours outside the domain enter with weight zero.
+// domains) tables and `other` indices are in the order of visit, outputs are
+// indexed by a.self (nullptr: by the position in the list), and neighbours
+// outside the domain enter with weight zero.
 // 4-byte words of LDS for the links of one site
 template <typename S, int MM>
 __host__ __device__ constexpr int hop_link_words() {
@@ -627,8 +629,8 @@ __global__ void __launch_bounds__(256, (HopWaves<S>::value)) hop_kernel(const Ho
   // them reads and computes its few directions only.  (Halo sites are 47% of
   // O1 and 38% of E2 for blocks of 8^3 x 16.  Hops 1 and 2 of 16^3 x 32, all
   // eight directions -> the live ones: FP32 Ls 16 261 -> 244 us, BF16 Ls 12
-  // with 8 sources 1295 -> 1227, F16 Ls 24 263 -> 260; three steps of the FP32
-  // block CG 1987 -> 1890.)  Four or more live directions keep the loads ahead.
+  // with 8 sources 1295 -> 1227, F16 Ls 24 263 -> 260; a block CG of six FP32
+  // steps 3974 -> 3773.)  Four or more live directions keep the loads ahead.
   constexpr bool kSparse = !GLOBAL && !DAG;
   constexpr int kSparseMost = 3;
   uint32_t live = 0;
@@ -712,6 +714,9 @@ __global__ void __launch_bounds__(256, (HopWaves<S>::value)) hop_kernel(const Ho
     const bool out = !GLOBAL && ((outm >> d) & 1);
     if constexpr (kH16) {
       hop_dir_h16<mu, sg, PRE, XM, MM>(lds, nthr, tid, s, Ls, pcu, pcl, raw, Lw + sl * 144 + d * 18, ra, rb, acc, out);
+    } else if constexpr (MM != 0) {
+      static_assert(!PRE, "M_phi mixes neighbouring s");
+      hop_dir_b16_mm<mu, sg>(raw, ra, rb, acc, out ? 0.f : raw.n);
     } else if constexpr (Traits<S>::kNorm) {
       hop_dir_norm<mu, sg, PRE, XM>(lds, nthr, tid, s, Ls, pcu, pcl, one, raw, U, acc, out);
     } else {
@@ -849,6 +854,12 @@ static size_t hop_lds_bytes(const HopArgs &a, int nthr, int epi, int dot, int xm
   return b;
 }
 
+// Types whose link products may run on the matrix cores: F16, and BF16 without
+// M_phi on the input
+template <typename S, int PRE> constexpr bool hop_can_mm() {
+  return std::is_same<S, _Float16>::value || (std::is_same<S, bf16>::value && !PRE);
+}
+
 template <typename S, int DAG, int PRE, int EPI, int DOT, int GLOBAL, int MM>
 static hipError_t launch_hop_t(const HopArgs &a, hipStream_t st) {
   const int xm = xmode(a.Ls, a.nrhs);
@@ -859,8 +870,8 @@ static hipError_t launch_hop_t(const HopArgs &a, hipStream_t st) {
   const size_t lds = hop_lds_bytes<S>(a, nthr, EPI, DOT, xm, MM);
   if (lds > kMaxLds) return hipErrorInvalidValue;
   switch (xm) {
-    case kXDpp16:  // (Ls = 16: F16 always on the matrix cores)
-      if constexpr (MM || !std::is_same<S, _Float16>::value)
+    case kXDpp16:  // (Ls = 16: always on the matrix cores where they are used at all)
+      if constexpr (MM || !hop_can_mm<S, PRE>())
         hipLaunchKernelGGL((hop_kernel<S, DAG, PRE, EPI, DOT, GLOBAL, kXDpp16, MM>), dim3(grid), blk, lds, st, a);
       break;
     case kXPerm: hipLaunchKernelGGL((hop_kernel<S, DAG, PRE, EPI, DOT, GLOBAL, kXPerm, MM>), dim3(grid), blk, lds, st, a); break;
@@ -874,15 +885,15 @@ int hop_groups_per_wave(int Ls, int nrhs) { return groups_per_wave(xmode(Ls, nrh
 
 template <typename S>
 static hipError_t dispatch_hop(int dagger, int pre, int epi, int dot, int global, const HopArgs &a, hipStream_t st) {
-  // F16 link products run on the matrix cores wherever the lanes of a site come
-  // in fours (every group of four lanes needs one link); other Ls take dot
-  // products.  Both sides on 24^3 x 64 x 24: 469 and 510 us a dslash_eo.
-  constexpr int kMM = std::is_same<S, _Float16>::value ? 1 : 0;
-  const bool mm = kMM && a.Ls % 4 == 0;
+  // F16 and BF16 link products run on the matrix cores wherever the lanes of a
+  // site come in fours (every group of four lanes needs one link); other Ls take
+  // dot products (F16, 24^3 x 64 x 24: 469 and 510 us a dslash_eo) or FP32
+  // multiply-adds (BF16 daggered, 16^3 x 32 x 24: 59.7 and 63.9 us).
+  const bool mm = a.Ls % 4 == 0;
   // the combinations used by the operators (anything else is rejected)
 #define MSPCG_HOP(D, P, E, T, G)                                                \
   if (dagger == D && pre == P && epi == E && dot == T && (global != 0) == (G != 0)) \
-    return mm ? launch_hop_t<S, D, P, E, T, G, kMM>(a, st) : launch_hop_t<S, D, P, E, T, G, 0>(a, st);
+    return mm ? launch_hop_t<S, D, P, E, T, G, hop_can_mm<S, P>()>(a, st) : launch_hop_t<S, D, P, E, T, G, 0>(a, st);
   MSPCG_HOP(0, 1, EPI_SCALE, 0, 1)          // M^4 in
   MSPCG_HOP(1, 0, EPI_MPHIDAG, 0, 1)        // (M^4)^+ in
   MSPCG_HOP(0, 1, EPI_M5INV, 0, 1)          // M_phi M_5^-1 M^4 in (first hop of D_PC)
