@@ -39,8 +39,8 @@ from paper_1811_08488_amd.workloads import WORKLOADS  # noqa: E402
 METRIC = "time-to-solution @1e-10 MSPCG vs plain CG (s); dslash GB/s & % HBM roofline"
 HBM_PEAK_GBS = 8000.0
 # Vector ALU ceiling: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz = 39.3 T lane
-# instructions per second, at 4 flops per instruction for the two-term dot
-# products (v_dot2_f32_f16) and packed operations the FP16 hop is built from
+# instructions per second, at 4 flops per instruction for two-term dot
+# products (v_dot2_f32_f16) and packed half operations
 VALU_PEAK_TFLOPS = 157.3
 # flops per 5D output site of a hop: the Wilson hop 1320 (8 directions x (12
 # for the spin projection + 2 x 66 for the link times two colour vectors) + 7 x 24
@@ -619,13 +619,13 @@ def main():
         "m5inv": m5,
         "block_hops": {f"hop{hop}_{pn}": {**v, "traffic": measured_traffic(w.name, f"block_hop{hop}_{pn}")}
                        for hop, v in bh.items()},
-        # the FP16 block hops are bound by vector-instruction issue (hardware
-        # counters: VALU busy about 3/4 of the launch, HBM about half), so the
-        # roofline is the vector ALU's; the HBM figures are kept beside it
-        "roofline": {"bound": "alu", "achieved": d["TFLOP/s"], "peak": VALU_PEAK_TFLOPS, "unit": "TFLOP/s",
-                     "frac": d["frac_valu"], "traffic": measured_traffic(w.name, f"block_hop{dom}_{pn}"),
-                     "algorithmic_flops": d["flops"], "algorithmic_bytes": d["bytes"], "hbm_GB/s": d["GB/s"],
-                     "hbm_frac": d["frac_hbm"], "avg_launch_us": d["us"],
+        # the block hops are bound by the memory traffic they cause (their
+        # neighbour re-reads move more than the algorithmic bytes, at the rate
+        # of a large copy); the arithmetic rate is kept beside it
+        "roofline": {"bound": "hbm", "achieved": d["GB/s"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                     "frac": d["frac_hbm"], "traffic": measured_traffic(w.name, f"block_hop{dom}_{pn}"),
+                     "algorithmic_flops": d["flops"], "algorithmic_bytes": d["bytes"],
+                     "alu_TFLOP/s": d["TFLOP/s"], "alu_frac": d["frac_valu"], "avg_launch_us": d["us"],
                      "kernel": f"hop_kernel<{pn}> block hop {dom} of the inner iteration "
                                f"({k * (outer + 1)} launches per solve)"},
     }
