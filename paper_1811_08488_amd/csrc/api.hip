@@ -360,8 +360,11 @@ int run_hop(mspcg_handle *h, int list_kind, int prec, int dag, int pre, int epi,
       HIPCHK(hipEventCreate(&e0));
       HIPCHK(hipEventCreate(&e1));
       float best = 0;
-      // (one timed launch of a candidate is enough where it takes 20 us or more)
-      const int reps = (size_t)a.nsites * a.nrhs * a.Ls * 24 * prec_bytes(prec) >= (64u << 20) ? 1 : 3;
+      // Two timed launches of a candidate where a field is 64 MB or more: a single
+      // one chose FP32 dslash_eo's shape on 24^3 x 64 x 24 wrongly in most runs
+      // (789 us instead of 730), three cost the first pass of source preparation
+      // 19.9 ms instead of 15.5.
+      const int reps = (size_t)a.nsites * a.nrhs * a.Ls * 24 * prec_bytes(prec) >= (64u << 20) ? 2 : 3;
       for (int c : cands) {
         const int thr = hop_threads(a.Ls, a.nrhs, c);
         if (thr > 256 || (thr < 64 && hop_threads(a.Ls, a.nrhs, 2 * c) <= 256 && c < kPad)) continue;
