@@ -204,12 +204,8 @@ struct mspcg_handle {
   std::map<std::vector<int>, int> tuned;
   bool autotune = true;
   int verbose = 0;  // MSPCG_VERBOSE=n: the solvers report progress on stderr every n outer iterations
-  // |r|^2 of the solvers' last two iterations, written by the device; a value
-  // is complete once its tag shows the iteration's number (never reused)
-  struct HostSlots {
-    double rr[2][MSPCG_MAX_NRHS];
-    int tag[2][MSPCG_MAX_NRHS];
-  } *slots = nullptr;
+  // the solvers' last two iterations, in pinned host memory (a tag is never reused)
+  HostSlot *slots = nullptr;
   int next_tag = 0;
   ~mspcg_handle() {
     if (work) (void)hipStreamSynchronize(work);
@@ -1006,7 +1002,8 @@ void more_sweeps(mspcg_handle *h, int nrhs, int sweeps, const Vec &z, const Vec 
 
 // ------------------------------------------------------------- solvers
 struct SolverWork {
-  double *rho, *pap, *alpha, *beta, *rr, *bb, *tmp, *rrt, *zrt, *zq;
+  double *scal;  // the rows below (ScalRow), `active` behind them
+  double *rho, *pap, *alpha, *beta, *rr, *bb, *tmp, *rrt, *zrt, *zq, *stop;
   int *active;
 };
 
@@ -1077,8 +1074,8 @@ mspcg_status solve(mspcg_handle *h, mspcg_field *x, const mspcg_field *b, const 
       ~Drain() { (void)hipStreamSynchronize(st); }
     } drain{st};
     if (!h->slots) {
-      HIPCHK(hipHostMalloc(reinterpret_cast<void **>(&h->slots), sizeof(*h->slots)));
-      std::memset(h->slots, 0, sizeof(*h->slots));
+      HIPCHK(hipHostMalloc(reinterpret_cast<void **>(&h->slots), 2 * sizeof(HostSlot)));
+      std::memset(h->slots, 0, 2 * sizeof(HostSlot));
     }
     const int nrhs = b->nrhs, Ls = h->par.Ls;
     const long long n = (long long)h->Vh * Ls * 24;
@@ -1090,20 +1087,14 @@ mspcg_status solve(mspcg_handle *h, mspcg_field *x, const mspcg_field *b, const 
     if (pc) h->sz.ensure(MSPCG_F64, nrhs, h->Vh, Ls);
     const size_t nparts_max = std::max<size_t>((size_t)std::max(h->Vh, kBlasGrid), bg ? (size_t)bg->be_tot : 0);
     h->partial.ensure(nparts_max * nrhs * sizeof(double));
-    h->scal.ensure((size_t)nrhs * 11 * sizeof(double) + 64);
+    h->scal.ensure((size_t)nrhs * kScalRows * sizeof(double) + MSPCG_MAX_NRHS * sizeof(int));
     double *part = h->partial.as<double>();
     SolverWork w;
-    w.rho = h->scal.as<double>();
-    w.pap = w.rho + nrhs;
-    w.alpha = w.pap + nrhs;
-    w.beta = w.alpha + nrhs;
-    w.rr = w.beta + nrhs;
-    w.bb = w.rr + nrhs;
-    w.tmp = w.bb + nrhs;
-    w.rrt = w.tmp + nrhs;
-    w.zrt = w.rrt + nrhs;
-    w.zq = w.zrt + nrhs;
-    w.active = reinterpret_cast<int *>(w.zq + nrhs);
+    w.scal = h->scal.as<double>();
+    double **const rows[kScalRows] = {&w.rho, &w.pap, &w.alpha, &w.beta, &w.rr, &w.bb,
+                                      &w.tmp, &w.rrt, &w.zrt,   &w.zq,   &w.stop};
+    for (int i = 0; i < kScalRows; ++i) *rows[i] = w.scal + i * nrhs;
+    w.active = reinterpret_cast<int *>(w.stop + nrhs);  // (behind `stop`: one copy to the device for both)
     PhaseTimer tm;
     tm.on = s->timing != 0;
     tm.st = st;
@@ -1113,7 +1104,9 @@ mspcg_status solve(mspcg_handle *h, mspcg_field *x, const mspcg_field *b, const 
     double *xd = (double *)X.data, *bd = (double *)B.data, *rd = (double *)R.data, *pd = (double *)P.data,
            *qd = (double *)Q.data, *zd = (double *)Z.data;
     std::vector<double> hb(nrhs), hr(nrhs);
+    std::vector<unsigned char> ctl(nrhs * (sizeof(double) + sizeof(int)));  // host copy of `stop` and `active`
     std::vector<int> active(nrhs, 1);
+    const double tol2 = s->tol * s->tol;
     auto norm2 = [&](const double *v, double *out) {
       HIPCHK(blas_dot_partial(v, v, n, nrhs, part, st));
       HIPCHK(blas_reduce(part, kBlasGrid, nrhs, out, st));
@@ -1125,8 +1118,14 @@ mspcg_status solve(mspcg_handle *h, mspcg_field *x, const mspcg_field *b, const 
       for (double v : hv)
         if (!std::isfinite(v)) fail(MSPCG_ENONFINITE, "non-finite value in a solver reduction");
     };
+    auto reached = [&](int i) { return active[i] && hr[i] <= tol2 * hb[i]; };
     auto push_active = [&] {
-      HIPCHK(hipMemcpyAsync(w.active, active.data(), nrhs * sizeof(int), hipMemcpyHostToDevice, st));
+      for (int i = 0; i < nrhs; ++i) {
+        const double stop = active[i] ? tol2 * hb[i] : -1.0;
+        std::memcpy(&ctl[i * sizeof(double)], &stop, sizeof(double));
+      }
+      std::memcpy(&ctl[nrhs * sizeof(double)], active.data(), nrhs * sizeof(int));
+      HIPCHK(hipMemcpyAsync(w.stop, ctl.data(), ctl.size(), hipMemcpyHostToDevice, st));
     };
     auto true_residual = [&] {  // r = b - A x, rr
       tm.mark(PhaseTimer::OP);
@@ -1185,7 +1184,9 @@ mspcg_status solve(mspcg_handle *h, mspcg_field *x, const mspcg_field *b, const 
     const bool fuse_p = pc && !s->flexible_beta && pc->n_sweeps <= 1;
     // x += alpha p waits for the direction update, which reads p anyway
     bool x_pending = false;
-    auto update_p = [&](bool first) {  // p = z (first) or z + beta p, with the pending x += alpha p
+    // p = z (first) or z + beta p, with the pending x += alpha p; ahead: p stays
+    // if the device finds that the iteration reached a tolerance
+    auto update_p = [&](bool first, bool ahead) {
       if (fuse_p) {
         tm.mark(PhaseTimer::PRECOND);
         HIPCHK(block_scatter_xpay(pc->inner_prec, block_args(h, bg, nrhs), P, x_pending ? xd : nullptr, bg->x.v,
@@ -1195,7 +1196,7 @@ mspcg_status solve(mspcg_handle *h, mspcg_field *x, const mspcg_field *b, const 
       } else if (first) {
         HIPCHK(blas_axpby(pd, 1.0, zd, 0.0, zd, n, nrhs, st));
       } else if (x_pending) {
-        HIPCHK(blas_update_xp(xd, pd, zd, w.alpha, w.beta, n, nrhs, st));
+        HIPCHK(blas_update_xp(xd, pd, zd, w.scal, n, nrhs, ahead, st));
       } else {
         HIPCHK(blas_xpay(pd, zd, w.beta, n, nrhs, st));
       }
@@ -1223,7 +1224,6 @@ mspcg_status solve(mspcg_handle *h, mspcg_field *x, const mspcg_field *b, const 
       }
       tm.mark(PhaseTimer::BLAS);
     };
-    const double tol2 = s->tol * s->tol;
     norm2(bd, w.bb);
     to_host(w.bb, hb);
     for (int i = 0; i < nrhs; ++i)
@@ -1233,7 +1233,7 @@ mspcg_status solve(mspcg_handle *h, mspcg_field *x, const mspcg_field *b, const 
       if (hb[i] == 0.0) HIPCHK(hipMemsetAsync(xd + (size_t)i * n, 0, n * sizeof(double), st));
     true_residual();
     for (int i = 0; i < nrhs; ++i)
-      if (active[i] && hr[i] <= tol2 * hb[i]) active[i] = 0;
+      if (reached(i)) active[i] = 0;
     push_active();
     int it = 0;
     long long inner = 0;
@@ -1243,34 +1243,35 @@ mspcg_status solve(mspcg_handle *h, mspcg_field *x, const mspcg_field *b, const 
     auto wait_rr = [&](int slot, int tag) {
       long spins = 0;
       for (int i = 0; i < nrhs; ++i) {
-        while (__atomic_load_n(&h->slots->tag[slot][i], __ATOMIC_ACQUIRE) != tag) {
+        while (__atomic_load_n(&h->slots[slot].tag[i], __ATOMIC_ACQUIRE) != tag) {
           __builtin_ia32_pause();
           if (++spins % 4096 != 0) continue;
           const hipError_t e = hipStreamQuery(st);
           (void)hipGetLastError();  // (not ready is no error of a later launch)
           if (e == hipErrorNotReady) continue;
           HIPCHK(e);
-          if (__atomic_load_n(&h->slots->tag[slot][i], __ATOMIC_ACQUIRE) != tag)
+          if (__atomic_load_n(&h->slots[slot].tag[i], __ATOMIC_ACQUIRE) != tag)
             fail(MSPCG_EHIP, "internal: the stream is idle and an iteration's residual was not reported");
         }
-        hr[i] = h->slots->rr[slot][i];
+        hr[i] = h->slots[slot].rr[i];
         if (!std::isfinite(hr[i])) fail(MSPCG_ENONFINITE, "non-finite value in a solver reduction");
       }
     };
     // Far from convergence plain CG's host looks at an iteration's |r|^2 only
-    // after it has enqueued the next iteration, so the device never waits for
-    // it (an outer iteration of MSPCG is hundreds of times that wait).  Far:
-    // the last known |r| of every right-hand side is more than kFar times the
-    // largest reduction seen in one iteration above its tolerance.  Should one
-    // fall further, the solve stops one iteration later: x, r and p are those
-    // of that iteration.
+    // after it has enqueued the next iteration, so the device never waits for it
+    // (an outer iteration of MSPCG is hundreds of times that wait).  If the
+    // iteration reached a tolerance after all, the device has kept p and rho, and
+    // the next one's alpha is 0, so that it keeps x, r, p and rho as well: the host
+    // drops that one and goes on from this state, as if it had waited.  Far: the
+    // last known |r| of every right-hand side is more than kFar times the largest
+    // reduction seen in one iteration above its tolerance, so that hardly an
+    // iteration is dropped.
     constexpr double kFar = 10.0;
     double drop = 0;  // largest |r_j|^2 / |r_{j+1}|^2 seen (0: none yet)
     std::vector<double> hr_last;
-    auto see = [&](bool next) {  // after hr was filled; next: by the iteration after hr_last's
-      if (next)
-        for (int i = 0; i < nrhs; ++i)
-          if (active[i] && hr[i] > 0) drop = std::max(drop, hr_last[i] / hr[i]);
+    auto see = [&] {  // after hr was filled by the iteration after hr_last's
+      for (int i = 0; i < nrhs; ++i)
+        if (active[i] && hr[i] > 0) drop = std::max(drop, hr_last[i] / hr[i]);
       hr_last = hr;
     };
     auto is_far = [&] {
@@ -1278,11 +1279,26 @@ mspcg_status solve(mspcg_handle *h, mspcg_field *x, const mspcg_field *b, const 
         if (active[i] && !(hr[i] > kFar * kFar * std::max(1.0, drop) * tol2 * hb[i])) return false;
       return drop > 0;
     };
-    see(false);
+    hr_last = hr;
+    // z = M^{-1} r, beta and p = z + beta p after an iteration (ahead: its reductions formed beta)
+    auto next_p = [&](bool ahead) {
+      precond();
+      if (pc) inner += (long long)pc->n_inner * std::max(1, pc->n_sweeps);
+      if (s->flexible_beta) {
+        // Polak-Ribiere: beta = <z', r' - r> / <z, r> with r' - r = -alpha A p
+        // (q still holds A p), i.e. beta = -<z', A p> / <p, A p>
+        HIPCHK(blas_dot_partial(zd, qd, n, nrhs, part, st));
+        HIPCHK(blas_reduce(part, kBlasGrid, nrhs, w.zq, st));
+        HIPCHK(solver_scalars(2, nrhs, w.active, w.rho, w.tmp, w.beta, st, w.zq, w.pap));
+      } else if (!ahead) {
+        HIPCHK(solver_scalars(1, nrhs, w.active, w.rho, pc ? w.tmp : w.rr, w.beta, st));
+      }
+      update_p(false, ahead);
+    };
     if (any) {
       precond();
       if (pc) inner += (long long)pc->n_inner * std::max(1, pc->n_sweeps);
-      update_p(true);  // p = z
+      update_p(true, false);  // p = z
       HIPCHK(hipMemcpyAsync(w.rho, w.tmp, nrhs * sizeof(double), hipMemcpyDeviceToDevice, st));
       int unseen = -1;  // the slot of the last iteration, if the host has not looked at it
       while (it < s->max_iter) {
@@ -1292,12 +1308,9 @@ mspcg_status solve(mspcg_handle *h, mspcg_field *x, const mspcg_field *b, const 
         const int slot = it & 1, tag = ++h->next_tag;
         ReduceOp pap_op, rr_op;
         pap_op.mode = 1;
-        pap_op.active = rr_op.active = w.active;
-        pap_op.rho = rr_op.rho = w.rho;
-        pap_op.res = w.alpha;
-        rr_op.res = w.beta;
-        rr_op.host = h->slots->rr[slot];
-        rr_op.host_tag = h->slots->tag[slot];
+        pap_op.ahead = unseen >= 0;
+        pap_op.scal = rr_op.scal = w.scal;
+        rr_op.host = h->slots + slot;
         rr_op.tag = tag;
         if (ahead) rr_op.mode = 2;  // rho_new = |r|^2
         tm.mark(PhaseTimer::OP);
@@ -1326,52 +1339,54 @@ mspcg_status solve(mspcg_handle *h, mspcg_field *x, const mspcg_field *b, const 
           x_pending = true;
         }
         ++it;
-        if (!ahead) {
-          wait_rr(slot, tag);
-          see(unseen < 0);
+        // looks at the iteration before, if that has not happened; if it reached a
+        // tolerance, this one changed nothing
+        bool dropped = false;
+        auto see_last = [&] {
+          if (unseen < 0) return;
+          wait_rr(unseen, tag - 1);
+          see();
           unseen = -1;
-          if (tm.on) HIPCHK(hipStreamSynchronize(st));
-          tm.drain();
-          bool check = false;
-          for (int i = 0; i < nrhs; ++i) check |= active[i] && hr[i] <= tol2 * hb[i];
-          if (check || reliable) {
-            finish_x();
-            true_residual();
-            bool changed = false;
-            for (int i = 0; i < nrhs; ++i)
-              if (active[i] && hr[i] <= tol2 * hb[i]) { active[i] = 0; changed = true; }
-            if (changed) push_active();
-          }
-          if (h->verbose > 0 && it % h->verbose == 0) {
-            double worst = 0;
-            for (int i = 0; i < nrhs; ++i)
-              if (hb[i] > 0) worst = std::max(worst, std::sqrt(hr[i] / hb[i]));
-            std::fprintf(stderr, "[mspcg] %s iteration %d: relative residual %.3e, %.1f s\n", pc ? "MSPCG" : "CG",
-                         it, worst, std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count());
-          }
-          any = false;
-          for (int a : active) any |= (a != 0);
-          if (!any) break;
-        }
-        precond();
-        if (pc) inner += (long long)pc->n_inner * std::max(1, pc->n_sweeps);
-        if (s->flexible_beta) {
-          // Polak-Ribiere: beta = <z', r' - r> / <z, r> with r' - r = -alpha A p
-          // (q still holds A p), i.e. beta = -<z', A p> / <p, A p>
-          HIPCHK(blas_dot_partial(zd, qd, n, nrhs, part, st));
-          HIPCHK(blas_reduce(part, kBlasGrid, nrhs, w.zq, st));
-          HIPCHK(solver_scalars(2, nrhs, w.active, w.rho, w.tmp, w.beta, st, w.zq, w.pap));
-        } else if (rr_op.mode != 2) {
-          HIPCHK(solver_scalars(1, nrhs, w.active, w.rho, pc ? w.tmp : w.rr, w.beta, st));
-        }
-        update_p(false);
+          for (int i = 0; i < nrhs; ++i) dropped |= reached(i);
+          if (dropped) --it, x_pending = false;
+        };
         if (ahead) {
-          if (unseen >= 0) {
-            wait_rr(unseen, tag - 1);
-            see(true);
+          next_p(true);
+          see_last();
+          if (!dropped) {
+            unseen = slot;
+            continue;
           }
-          unseen = slot;
+        } else {
+          see_last();
+          if (!dropped) {
+            wait_rr(slot, tag);
+            see();
+          }
         }
+        if (tm.on) HIPCHK(hipStreamSynchronize(st));
+        tm.drain();
+        bool check = false;
+        for (int i = 0; i < nrhs; ++i) check |= reached(i);
+        if (check || reliable) {
+          finish_x();
+          true_residual();
+          bool changed = false;
+          for (int i = 0; i < nrhs; ++i)
+            if (reached(i)) { active[i] = 0; changed = true; }
+          if (changed) push_active();
+        }
+        if (h->verbose > 0 && it % h->verbose == 0) {
+          double worst = 0;
+          for (int i = 0; i < nrhs; ++i)
+            if (hb[i] > 0) worst = std::max(worst, std::sqrt(hr[i] / hb[i]));
+          std::fprintf(stderr, "[mspcg] %s iteration %d: relative residual %.3e, %.1f s\n", pc ? "MSPCG" : "CG", it,
+                       worst, std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count());
+        }
+        any = false;
+        for (int a : active) any |= (a != 0);
+        if (!any) break;
+        next_p(false);
       }
       finish_x();
     }
@@ -1662,7 +1677,7 @@ mspcg_status local_block_cg(mspcg_handle *h, mspcg_field *z, const mspcg_field *
     HIPCHK(blas_reduce(h->partial.as<double>(), kBlasGrid, nrhs, rr, st));
     run_block_cg(h, bg, pc->inner_prec, nrhs, pc->n_inner, pc->inner_tol, Zv, Rv, rr, nullptr, nullptr, st);
     if (pc->n_sweeps > 1) {
-      h->scal.ensure((size_t)nrhs * 11 * sizeof(double) + 64);
+      h->scal.ensure((size_t)nrhs * kScalRows * sizeof(double) + MSPCG_MAX_NRHS * sizeof(int));
       more_sweeps(h, nrhs, pc->n_sweeps, Zv, Rv, h->scal.as<double>(), h->partial.as<double>(), st,
                   [&](const Vec &z2, const Vec &t, double *rrt) {
                     run_block_cg(h, bg, pc->inner_prec, nrhs, pc->n_inner, pc->inner_tol, z2, t, rrt, nullptr,

@@ -107,16 +107,28 @@ hipError_t launch_convert(const Vec &out, const Vec &in, int nrhs, long long nsi
 constexpr int kBlasWG = 256;
 constexpr int kBlasGrid = 512;  // workgroups per right-hand side (fixed: deterministic sums)
 hipError_t blas_dot_partial(const double *a, const double *b, long long n, int nrhs, double *partial, hipStream_t st);
-// What a reduction forms from its sum v per right-hand side (device arrays
-// [nrhs]): mode 0 nothing more; 1: res = alpha = active ? rho / v : 0 (v = <p, A p>);
-// 2: res = beta = active ? v / rho : 0 and rho = v (v = rho_new).  With `host`
-// the sum also goes to host memory, followed by `tag` in host_tag.
+// Scalars of a solve: rows of nrhs values in one device buffer.
+enum ScalRow {
+  kRho, kPap, kAlpha, kBeta, kRR, kBB, kTmp, kRRt, kZRt, kZQ,
+  kStop,  // |r|^2 at which a right-hand side has reached its tolerance; -1: it is not active
+  kScalRows
+};
+// |r|^2 as the device reports it to the host: a value is complete once its tag shows the iteration's number
+struct HostSlot {
+  double rr[MSPCG_MAX_NRHS];
+  int tag[MSPCG_MAX_NRHS];
+};
+// What a reduction forms from its sum v per right-hand side, in the rows of
+// `scal`: mode 0 nothing more; 1: alpha = active ? rho / v : 0 (v = <p, A p>);
+// 2: beta = active ? v / rho : 0 (v = |r|^2 = rho_new), but -1 where v <= stop.
+// With `host` the sum also goes to host memory.
+// An iteration that is enqueued before the host has seen the last one's |r|^2
+// takes place unless the last one reached a tolerance: in mode 1 with `ahead`, if
+// some beta is negative, alpha = 0 and rho stays, else rho = rr first.
 struct ReduceOp {
-  int mode = 0;
-  const int *active = nullptr;
-  double *rho = nullptr, *res = nullptr;
-  double *host = nullptr;
-  int *host_tag = nullptr;
+  int mode = 0, ahead = 0;
+  double *scal = nullptr;
+  HostSlot *host = nullptr;
   int tag = 0;
 };
 hipError_t blas_reduce(const double *partial, int nparts, int nrhs, double *out, hipStream_t st,
@@ -126,9 +138,10 @@ hipError_t blas_update_xr(double *x, double *r, const double *p, const double *q
                           int nrhs, double *partial, hipStream_t st);
 // p = z + beta p
 hipError_t blas_xpay(double *p, const double *z, const double *beta, long long n, int nrhs, hipStream_t st);
-// x += alpha p, then p = z + beta p (alpha, beta: device arrays [nrhs])
-hipError_t blas_update_xp(double *x, double *p, const double *z, const double *alpha, const double *beta, long long n,
-                          int nrhs, hipStream_t st);
+// x += alpha p, then p = z + beta p (alpha, beta: rows of scal); ahead: p stays if
+// some beta is negative (a reduction's mode 2)
+hipError_t blas_update_xp(double *x, double *p, const double *z, const double *scal, long long n, int nrhs, int ahead,
+                          hipStream_t st);
 // x += alpha p (alpha: device array [nrhs])
 hipError_t blas_axpy(double *x, const double *p, const double *alpha, long long n, int nrhs, hipStream_t st);
 // out = a x + b y (host scalars)

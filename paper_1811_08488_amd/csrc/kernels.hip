@@ -1081,6 +1081,18 @@ __global__ void __launch_bounds__(kReduceWG) k_reduce(const double *partial, int
                                                       const ReduceOp op) {
   __shared__ double sh[kReduceWG / 64];
   const int r = blockIdx.x;
+  // The scalars of the solvers are requested with the partial sums, not after
+  // them, and as vector loads (scalar ones would all be waited for before the
+  // first partial sum is requested).
+  double rho = 0, rho_new = 0, stop = -1, last_beta = 0;
+  if (op.scal) {
+    int vr = r;
+    asm("" : "+v"(vr));
+    rho = op.scal[kRho * nrhs + vr];
+    rho_new = op.scal[kRR * nrhs + vr];
+    stop = op.scal[kStop * nrhs + vr];
+    last_beta = op.scal[kBeta * nrhs + min((int)(threadIdx.x & 63), nrhs - 1)];
+  }
   double acc[kReduceStrands];
 #pragma unroll
   for (int j = 0; j < kReduceStrands; ++j) acc[j] = 0;
@@ -1100,21 +1112,21 @@ __global__ void __launch_bounds__(kReduceWG) k_reduce(const double *partial, int
   for (int w = 32; w > 0; w >>= 1) v += __shfl_down(v, w, 64);
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
   __syncthreads();
+  const bool on = stop >= 0.0, dropped = op.ahead && __ballot(last_beta < 0.0) != 0;
   if (threadIdx.x != 0) return;
   v = 0;
 #pragma unroll
   for (int w = 0; w < kReduceWG / 64; ++w) v += sh[w];
   out[r] = v;
   if (op.mode == 1) {  // v = <p, A p>
-    op.res[r] = (op.active[r] != 0 && v != 0.0) ? op.rho[r] / v : 0.0;
+    if (op.ahead && on && !dropped) op.scal[kRho * nrhs + r] = rho = rho_new;
+    op.scal[kAlpha * nrhs + r] = (on && !dropped && v != 0.0) ? rho / v : 0.0;
   } else if (op.mode == 2) {  // v = rho_new
-    const bool on = op.active[r] != 0;
-    op.res[r] = (on && op.rho[r] != 0.0) ? v / op.rho[r] : 0.0;
-    if (on) op.rho[r] = v;
+    op.scal[kBeta * nrhs + r] = v <= stop ? -1.0 : (on && rho != 0.0) ? v / rho : 0.0;
   }
   if (op.host) {  // the value, then its tag, in host memory
-    __hip_atomic_store(op.host + r, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    __hip_atomic_store(op.host_tag + r, op.tag, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(op.host->rr + r, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(op.host->tag + r, op.tag, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
   }
 }
 
@@ -1174,10 +1186,13 @@ hipError_t blas_xpay(double *p, const double *z, const double *beta, long long n
 // x += alpha p and p = z + beta p in one pass (the x update of an iteration
 // waits for beta: five passes over memory instead of the 3 + 3 of an update of
 // x and one of p).  Bound by memory.
-__global__ void __launch_bounds__(kBlasWG) k_update_xp(double *xv, double *pv, const double *zv, const double *alpha,
-                                                       const double *beta, long long n) {
+__global__ void __launch_bounds__(kBlasWG) k_update_xp(double *xv, double *pv, const double *zv, const double *scal,
+                                                       long long n, int nrhs, int ahead) {
   const int r = blockIdx.y;
-  const double al = alpha[r], be = beta[r];
+  const double *beta = scal + kBeta * nrhs;
+  const double al = scal[kAlpha * nrhs + r], be = beta[r];
+  double any_be = 0;
+  if (nrhs > 1) any_be = beta[min((int)(threadIdx.x & 63), nrhs - 1)];
   double2 *x = reinterpret_cast<double2 *>(xv + (size_t)r * n);
   double2 *p = reinterpret_cast<double2 *>(pv + (size_t)r * n);
   const double2 *z = reinterpret_cast<const double2 *>(zv + (size_t)r * n);
@@ -1190,13 +1205,14 @@ __global__ void __launch_bounds__(kBlasWG) k_update_xp(double *xv, double *pv, c
     pi.x = zi.x + be * pi.x;
     pi.y = zi.y + be * pi.y;
     store16(x + i, xi);
-    store16(p + i, pi);
+    // (seen by the first lanes of a wave, 32 at least: n2 is a multiple of 32)
+    if (!(ahead && (nrhs == 1 ? be < 0.0 : __ballot(any_be < 0.0) != 0))) store16(p + i, pi);
   }
 }
 
-hipError_t blas_update_xp(double *x, double *p, const double *z, const double *alpha, const double *beta, long long n,
-                          int nrhs, hipStream_t st) {
-  hipLaunchKernelGGL(k_update_xp, dim3(kBlasGrid, nrhs), dim3(kBlasWG), 0, st, x, p, z, alpha, beta, n);
+hipError_t blas_update_xp(double *x, double *p, const double *z, const double *scal, long long n, int nrhs, int ahead,
+                          hipStream_t st) {
+  hipLaunchKernelGGL(k_update_xp, dim3(kBlasGrid, nrhs), dim3(kBlasWG), 0, st, x, p, z, scal, n, nrhs, ahead);
   return hipGetLastError();
 }
 
