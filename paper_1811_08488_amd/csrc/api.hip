@@ -343,10 +343,18 @@ int run_hop(mspcg_handle *h, int list_kind, int prec, int dag, int pre, int epi,
         if ((G * w) % a.nrhs == 0 && allowed(G * w / a.nrhs) &&
             std::find(cands.begin(), cands.end(), G * w / a.nrhs) == cands.end())
           cands.push_back(G * w / a.nrhs);
+    // default: the fullest workgroup of whole waves, else the largest power of
+    // two, of those whose links and exchange rows fit the LDS (FP64 at Ls = 2: not 128 sites)
+    auto fits = [&](int c) {
+      HopArgs b = a;
+      b.nsite_wg = c;
+      return hop_fits(prec, pre, epi, dot, b);
+    };
     int n0 = pick_nsite(a.nrhs, a.Ls);
-    if (G > 0)  // default: the fullest workgroup of whole waves
+    while (n0 > 1 && !fits(n0)) n0 /= 2;
+    if (G > 0)
       for (int w = 4; w >= 1; --w)
-        if ((G * w) % a.nrhs == 0 && allowed(G * w / a.nrhs) && hop_threads(a.Ls, a.nrhs, G * w / a.nrhs) <= 256) {
+        if ((G * w) % a.nrhs == 0 && allowed(G * w / a.nrhs) && fits(G * w / a.nrhs)) {
           n0 = G * w / a.nrhs;
           break;
         }

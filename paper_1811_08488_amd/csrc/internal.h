@@ -78,6 +78,8 @@ struct HopArgs {
 int hop_threads(int Ls, int nrhs, int nsite_wg);
 // (site, rhs) groups per 64-lane wave of that layout (0: densely packed lanes)
 int hop_groups_per_wave(int Ls, int nrhs);
+// a launch of this variant with a.nsite_wg sites per workgroup keeps within a workgroup's threads and LDS
+bool hop_fits(int prec, int pre, int epi, int dot, const HopArgs &a);
 
 // Launch the hop kernel for storage `prec`; returns hipSuccess or the launch error.
 hipError_t launch_hop(int prec, int dagger, int pre_mphi, int epi, int dot, int global, const HopArgs &a,

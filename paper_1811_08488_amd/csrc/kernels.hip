@@ -883,6 +883,18 @@ static hipError_t launch_hop_t(const HopArgs &a, hipStream_t st) {
 int hop_threads(int Ls, int nrhs, int nsite_wg) { return layout_threads(xmode(Ls, nrhs), Ls, nrhs * nsite_wg); }
 int hop_groups_per_wave(int Ls, int nrhs) { return groups_per_wave(xmode(Ls, nrhs), Ls); }
 
+bool hop_fits(int prec, int pre, int epi, int dot, const HopArgs &a) {
+  const int nthr = hop_threads(a.Ls, a.nrhs, a.nsite_wg), xm = xmode(a.Ls, a.nrhs), mm = a.Ls % 4 == 0;
+  size_t lds = 0;
+  switch (prec) {
+    case MSPCG_F64: lds = hop_lds_bytes<double>(a, nthr, epi, dot, xm, 0); break;
+    case MSPCG_F32: lds = hop_lds_bytes<float>(a, nthr, epi, dot, xm, 0); break;
+    case MSPCG_F16: lds = hop_lds_bytes<_Float16>(a, nthr, epi, dot, xm, mm); break;
+    default: lds = hop_lds_bytes<bf16>(a, nthr, epi, dot, xm, mm && !pre); break;
+  }
+  return nthr <= 256 && lds <= kMaxLds;
+}
+
 template <typename S>
 static hipError_t dispatch_hop(int dagger, int pre, int epi, int dot, int global, const HopArgs &a, hipStream_t st) {
   // F16 and BF16 link products run on the matrix cores wherever the lanes of a
