@@ -115,31 +115,41 @@ __device__ inline void load24(const bf16 *base, const float *norm, size_t site4,
   }
 }
 
-// A 16-byte store that the caches need not keep.  Every field is far larger
-// than an XCD's L2 and its next reader is another launch, so a written line
-// that stays in L2 only displaces inputs that neighbouring sites still need.
-// With ordinary -> with these stores: FP32 A on 16^3 x 32 x 16 309 -> 298 us,
-// FP64 CG there 304 -> 296 ms, block CG FP32 k = 6 4249 -> 4109 us, MSPCG F16
-// k = 8 at Ls = 24 828 -> 801 ms; the BF16 hop, then bound by vector issue, lost
-// 0.6% and keeps ordinary stores.
+// A 16-byte store that the caches need not keep.  Where a field is larger than
+// an XCD's 4 MB L2, its next reader (another launch) finds it evicted anyway, and
+// a written line that stays only displaces inputs that neighbouring sites still
+// need.  Ordinary -> these stores: FP32 A on 16^3 x 32 x 16 303 -> 292 us, block CG
+// FP32 k = 6 there 3971 -> 3811, source preparation and reconstruction 703 -> 676,
+// FP64 A on 24^3 x 64 x 24 6379 -> 6335, F16 dslash_eo 443 -> 429.  Smaller fields,
+// whose next reader could still hit, do not mind: FP64 dslash_eo on 8^4 x 8 7.88 ->
+// 7.83 us, CG on 4^4 x 8 2838 -> 2843 (means of twelve processes, which differ by 1%).
+// (M_5^{-1} and conversions, which only stream, take them by the length of a row:
+// see op5_kernel.)
+// BF16 fields take ordinary stores, chosen when the BF16 hop was bound by vector
+// issue (0.6% faster then).  With the present hop, ordinary / non-temporal, us:
+// 16^3 x 32, eight sources of Ls 12: daggered hop 278 / 278, A 1281 / 1290, block
+// hops 1-4 2147 / 2126; Ls 16: A 175 / 182, block hops 307 / 256; 24^3 x 64 x 24:
+// daggered hop 382 / 366, A 1890 / 1850, block hops 2727 / 2640.
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-template <typename T>
+template <bool NT = true, typename T>
 __device__ inline void store16(void *p, const T &v) {
-  __builtin_nontemporal_store(__builtin_bit_cast(u32x4, v), reinterpret_cast<u32x4 *>(p));
+  const u32x4 u = __builtin_bit_cast(u32x4, v);
+  if (NT) __builtin_nontemporal_store(u, reinterpret_cast<u32x4 *>(p));
+  else *reinterpret_cast<u32x4 *>(p) = u;
 }
 
-template <typename R>
+template <typename R, bool NT = true>
 __device__ inline void store24(double *base, float *, size_t site4, int s, int Ls, const R v[24]) {
 #pragma unroll
   for (int k = 0; k < 12; ++k)
-    store16(base + chunk_index<double>(site4, s, Ls, k), make_double2((double)v[2 * k], (double)v[2 * k + 1]));
+    store16<NT>(base + chunk_index<double>(site4, s, Ls, k), make_double2((double)v[2 * k], (double)v[2 * k + 1]));
 }
-template <typename R>
+template <typename R, bool NT = true>
 __device__ inline void store24(float *base, float *, size_t site4, int s, int Ls, const R v[24]) {
 #pragma unroll
   for (int k = 0; k < 6; ++k)
-    store16(base + chunk_index<float>(site4, s, Ls, k),
-            make_float4((float)v[4 * k], (float)v[4 * k + 1], (float)v[4 * k + 2], (float)v[4 * k + 3]));
+    store16<NT>(base + chunk_index<float>(site4, s, Ls, k),
+                make_float4((float)v[4 * k], (float)v[4 * k + 1], (float)v[4 * k + 2], (float)v[4 * k + 3]));
 }
 template <typename R>
 __device__ inline float site_scale(const R v[24], float &inv) {
@@ -151,7 +161,7 @@ __device__ inline float site_scale(const R v[24], float &inv) {
   inv = m > 0.f ? __builtin_amdgcn_rcpf(m) : 0.f;
   return m;
 }
-template <typename R>
+template <typename R, bool NT = true>
 __device__ inline void store24(_Float16 *base, float *norm, size_t site4, int s, int Ls, const R v[24]) {
   float inv;
   norm[site4 * Ls + s] = site_scale(v, inv);
@@ -165,10 +175,10 @@ __device__ inline void store24(_Float16 *base, float *norm, size_t site4, int s,
       c.h[1] = (_Float16)((float)v[8 * k + 2 * j + 1] * inv);
       w[j] = c.u;
     }
-    store16(base + chunk_index<_Float16>(site4, s, Ls, k), make_uint4(w[0], w[1], w[2], w[3]));
+    store16<NT>(base + chunk_index<_Float16>(site4, s, Ls, k), make_uint4(w[0], w[1], w[2], w[3]));
   }
 }
-template <typename R>
+template <typename R, bool NT = true>
 __device__ inline void store24(bf16 *base, float *norm, size_t site4, int s, int Ls, const R v[24]) {
   float inv;
   norm[site4 * Ls + s] = site_scale(v, inv);

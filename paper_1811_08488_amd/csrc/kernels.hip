@@ -941,7 +941,20 @@ hipError_t launch_hop(int prec, int dagger, int pre, int epi, int dot, int globa
 }
 
 // ---------------------------------------------------------------- fifth-dimension operator
-template <typename S, int XM>
+// Non-temporal stores (NT) pay only where a wave fills the lines it writes: a
+// store instruction writes one row of Ls x 16 bytes per site, and a line that
+// holds the ends of two rows, or a site shared by two waves, reaches memory in
+// parts.  They are used for rows of whole 64-byte segments (Ls a multiple of
+// four), and for other Ls where a wave holds whole sites and a row has a segment
+// of its own (FP64, with the most rows: Ls >= 8).  M_5^{-1}, ordinary -> non-temporal,
+// us, used: FP64 Ls 24 on 24^3 x 48 570 -> 561, Ls 14 on 16^3 x 32 74 -> 63; FP32 Ls 6 and
+// 16 on 24^3 x 48 90 -> 74 and 187 -> 180, F16 Ls 10 111 -> 83; not used: FP64 Ls 2 59 ->
+// 81, Ls 5 167 -> 175, Ls 11 (packed lanes) 246 -> 317, FP32 Ls 13 (packed) 153 -> 194.
+static bool op5_nontemporal(int prec, int Ls, int nrhs) {
+  return Ls % 4 == 0 || (hop_groups_per_wave(Ls, nrhs) > 0 && Ls >= (prec == MSPCG_F64 ? 8 : 5));
+}
+
+template <typename S, int XM, bool NT>
 __global__ void __launch_bounds__(256) op5_kernel(const Op5Args a) {
   using R = typename Traits<S>::R;
   extern __shared__ __align__(16) unsigned char smem[];
@@ -977,15 +990,15 @@ __global__ void __launch_bounds__(256) op5_kernel(const Op5Args a) {
     pchi_comb<1, XM, R>(lds, nthr, tid, s, Ls, (R)a.a, (R)a.b, (R)a.mf, v);
   else
     pchi_comb<0, XM, R>(lds, nthr, tid, s, Ls, (R)a.a, (R)a.b, (R)a.mf, v);
-  if (active) store24<R>(reinterpret_cast<S *>(a.out), a.out_norm, idx, s, Ls, v);
+  if (active) store24<R, NT>(reinterpret_cast<S *>(a.out), a.out_norm, idx, s, Ls, v);
 }
 
-template <typename S>
+template <typename S, bool NT>
 static void launch_op5_t(const Op5Args &a, dim3 grid, dim3 blk, size_t lds, hipStream_t st) {
   switch (xmode(a.Ls, a.nrhs)) {
-    case kXDpp16: hipLaunchKernelGGL((op5_kernel<S, kXDpp16>), grid, blk, lds, st, a); break;
-    case kXPerm: hipLaunchKernelGGL((op5_kernel<S, kXPerm>), grid, blk, lds, st, a); break;
-    default: hipLaunchKernelGGL((op5_kernel<S, kXLds>), grid, blk, lds, st, a); break;
+    case kXDpp16: hipLaunchKernelGGL((op5_kernel<S, kXDpp16, NT>), grid, blk, lds, st, a); break;
+    case kXPerm: hipLaunchKernelGGL((op5_kernel<S, kXPerm, NT>), grid, blk, lds, st, a); break;
+    default: hipLaunchKernelGGL((op5_kernel<S, kXLds, NT>), grid, blk, lds, st, a); break;
   }
 }
 
@@ -997,44 +1010,56 @@ hipError_t launch_op5(int prec, const Op5Args &a, hipStream_t st) {
   const size_t rsz = (prec == MSPCG_F64) ? 8 : 4;
   const size_t lds = (size_t)kRow * nthr * rsz;
   const dim3 blk = (xm == kXLds) ? dim3(a.Ls, a.nrhs, a.nsite_wg) : dim3(nthr);
+  const bool nt = op5_nontemporal(prec, a.Ls, a.nrhs);
+#define MSPCG_OP5(S) nt ? launch_op5_t<S, true>(a, dim3(grid), blk, lds, st) : launch_op5_t<S, false>(a, dim3(grid), blk, lds, st)
   switch (prec) {
-    case MSPCG_F64: launch_op5_t<double>(a, dim3(grid), blk, lds, st); break;
-    case MSPCG_F32: launch_op5_t<float>(a, dim3(grid), blk, lds, st); break;
-    case MSPCG_F16: launch_op5_t<_Float16>(a, dim3(grid), blk, lds, st); break;
-    case MSPCG_BF16: launch_op5_t<bf16>(a, dim3(grid), blk, lds, st); break;
+    case MSPCG_F64: MSPCG_OP5(double); break;
+    case MSPCG_F32: MSPCG_OP5(float); break;
+    case MSPCG_F16: MSPCG_OP5(_Float16); break;
+    case MSPCG_BF16: launch_op5_t<bf16, false>(a, dim3(grid), blk, lds, st); break;
     default: return hipErrorInvalidValue;
   }
+#undef MSPCG_OP5
   return hipGetLastError();
 }
 
 // ---------------------------------------------------------------- conversion
-template <typename SO, typename SI>
+// Non-temporal stores as in op5_kernel; the lanes are packed, so only rows of
+// whole 128-byte lines, or of whole 64-byte segments and more than two lines,
+// gain.  Ordinary -> non-temporal, us, 24^3 x 48, used: FP64 to FP64 Ls 24 567 -> 546,
+// FP32 to FP64 Ls 8 146 -> 110, FP64 to FP64 Ls 20 on 16^3 x 32 94 -> 79; not used: FP64 to
+// FP64 Ls 2 40 -> 117, 5 118 -> 220, 10 246 -> 306, 12 294 -> 307, F16 to FP64 Ls 5 97 -> 190.
+template <typename SO, typename SI, bool NT>
 __global__ void convert_kernel(SO *out, float *out_norm, const SI *in, const float *in_norm, long long n5, int Ls) {
   const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n5) return;
   const size_t site4 = (size_t)(i / Ls);
   const int s = (int)(i % Ls);
-  if (sizeof(SI) == 8 || sizeof(SO) == 8) {
-    double t[24];
-    load24<double>(in, in_norm, site4, s, Ls, t);
-    store24<double>(out, out_norm, site4, s, Ls, t);
-  } else {
-    float v[24];
-    load24<float>(in, in_norm, site4, s, Ls, v);
-    store24<float>(out, out_norm, site4, s, Ls, v);
-  }
+  using T = typename std::conditional<sizeof(SI) == 8 || sizeof(SO) == 8, double, float>::type;
+  T v[24];
+  load24<T>(in, in_norm, site4, s, Ls, v);
+  store24<T, NT>(out, out_norm, site4, s, Ls, v);
+}
+
+template <typename SO, typename SI>
+static void launch_convert_t(const Vec &out, const Vec &in, long long n5, int Ls, hipStream_t st) {
+  const int blk = 256;
+  const dim3 grid((n5 + blk - 1) / blk);
+  SO *o = reinterpret_cast<SO *>(out.data);
+  const SI *i = reinterpret_cast<const SI *>(in.data);
+  if (Ls % 8 == 0 || (Ls % 4 == 0 && Ls > 16))
+    hipLaunchKernelGGL((convert_kernel<SO, SI, true>), grid, dim3(blk), 0, st, o, out.norm, i, in.norm, n5, Ls);
+  else
+    hipLaunchKernelGGL((convert_kernel<SO, SI, false>), grid, dim3(blk), 0, st, o, out.norm, i, in.norm, n5, Ls);
 }
 
 template <typename SO>
 static hipError_t convert_from(const Vec &out, const Vec &in, long long n5, int Ls, hipStream_t st) {
-  const int blk = 256;
-  const long long grid = (n5 + blk - 1) / blk;
-  SO *o = reinterpret_cast<SO *>(out.data);
   switch (in.prec) {
-    case MSPCG_F64: hipLaunchKernelGGL((convert_kernel<SO, double>), dim3(grid), dim3(blk), 0, st, o, out.norm, (const double *)in.data, in.norm, n5, Ls); break;
-    case MSPCG_F32: hipLaunchKernelGGL((convert_kernel<SO, float>), dim3(grid), dim3(blk), 0, st, o, out.norm, (const float *)in.data, in.norm, n5, Ls); break;
-    case MSPCG_F16: hipLaunchKernelGGL((convert_kernel<SO, _Float16>), dim3(grid), dim3(blk), 0, st, o, out.norm, (const _Float16 *)in.data, in.norm, n5, Ls); break;
-    case MSPCG_BF16: hipLaunchKernelGGL((convert_kernel<SO, bf16>), dim3(grid), dim3(blk), 0, st, o, out.norm, (const bf16 *)in.data, in.norm, n5, Ls); break;
+    case MSPCG_F64: launch_convert_t<SO, double>(out, in, n5, Ls, st); break;
+    case MSPCG_F32: launch_convert_t<SO, float>(out, in, n5, Ls, st); break;
+    case MSPCG_F16: launch_convert_t<SO, _Float16>(out, in, n5, Ls, st); break;
+    case MSPCG_BF16: launch_convert_t<SO, bf16>(out, in, n5, Ls, st); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
