@@ -1323,7 +1323,7 @@ __device__ inline void block_mphi(R *lds, int nthr, int tid, int s, int Ls, cons
   pchi_comb<0, kXLds, R>(lds, nthr, tid, s, Ls, (R)b.mphi_b, (R)b.mphi_c, (R)b.mf, v);
 }
 
-template <typename S>
+template <typename S, bool NT>
 __global__ void __launch_bounds__(256) k_block_gather(const BlockArgs b, Vec xs, Vec rs, Vec ps, Vec mps,
                                                        const double *rg, long long rg_stride, const double *rr,
                                                        double n_total, double *partial) {
@@ -1343,14 +1343,14 @@ __global__ void __launch_bounds__(256) k_block_gather(const BlockArgs b, Vec xs,
     load24<double>(rg, nullptr, (size_t)r * rg_stride + cb, s, Ls, t);
 #pragma unroll
     for (int k = 0; k < 24; ++k) v[k] = (R)(scale * t[k]);
-    store24<R>(reinterpret_cast<S *>(rs.data), rs.norm, o, s, Ls, v);
+    store24<R, NT>(reinterpret_cast<S *>(rs.data), rs.norm, o, s, Ls, v);
     // the values as stored, so that r and p start identical and the sum matches them
     stored_values<S>(v);
-    store24<R>(reinterpret_cast<S *>(ps.data), ps.norm, o, s, Ls, v);
+    store24<R, NT>(reinterpret_cast<S *>(ps.data), ps.norm, o, s, Ls, v);
     if (xs.data) {  // (the fixed-k solve sets x in its first update instead)
       R z[24];
       zero24(z);
-      store24<R>(reinterpret_cast<S *>(xs.data), xs.norm, o, s, Ls, z);
+      store24<R, NT>(reinterpret_cast<S *>(xs.data), xs.norm, o, s, Ls, z);
     }
     R acc = 0;
 #pragma unroll
@@ -1358,11 +1358,11 @@ __global__ void __launch_bounds__(256) k_block_gather(const BlockArgs b, Vec xs,
     val = (double)acc;
   }
   block_mphi<R>(reinterpret_cast<R *>(smem), nthr, tid, s, Ls, b, v);
-  if (cb >= 0) store24<R>(reinterpret_cast<S *>(mps.data), mps.norm, o, s, Ls, v);
+  if (cb >= 0) store24<R, NT>(reinterpret_cast<S *>(mps.data), mps.norm, o, s, Ls, v);
   wg_partial(reinterpret_cast<double *>(smem), nthr, tid, Ls, b.nrhs, b.nsite_wg, 0, val, partial, blockIdx.x);
 }
 
-template <typename S>
+template <typename S, bool NT>
 __global__ void __launch_bounds__(256) k_block_scatter(const BlockArgs b, double *zg, long long zg_stride, Vec xs,
                                                         Vec ps, const double *scal, int mode, const double *rg,
                                                         long long rg_stride, const double *rr, double n_total,
@@ -1390,7 +1390,7 @@ __global__ void __launch_bounds__(256) k_block_scatter(const BlockArgs b, double
     double z[24], t[24];
 #pragma unroll
     for (int k = 0; k < 24; ++k) z[k] = inv * (double)v[k];
-    if (zg) store24<double>(zg, nullptr, (size_t)r * zg_stride + cb, s, Ls, z);  // (none: only the partials)
+    if (zg) store24<double, NT>(zg, nullptr, (size_t)r * zg_stride + cb, s, Ls, z);  // (none: only the partials)
     if (rg) {
       load24<double>(rg, nullptr, (size_t)r * rg_stride + cb, s, Ls, t);
 #pragma unroll
@@ -1404,7 +1404,7 @@ __global__ void __launch_bounds__(256) k_block_scatter(const BlockArgs b, double
 // beta p(cb) (first: p = v / scale) with v as in k_block_scatter, so the
 // preconditioned residual z is never stored.  With xg the outer solution's
 // pending update x += alpha p happens here too, where p is read anyway.
-template <typename S>
+template <typename S, bool NT>
 __global__ void __launch_bounds__(256) k_block_scatter_xpay(const BlockArgs b, double *pg, double *xg,
                                                              long long pg_stride, Vec xs, Vec ps, const double *scal,
                                                              int mode, const double *rr, double n_total,
@@ -1440,15 +1440,15 @@ __global__ void __launch_bounds__(256) k_block_scatter_xpay(const BlockArgs b, d
       load24<double>(xg, nullptr, g, s, Ls, x);
 #pragma unroll
       for (int k = 0; k < 24; ++k) x[k] = fma(oal, pn[k], x[k]);
-      store24<double>(xg, nullptr, g, s, Ls, x);
+      store24<double, NT>(xg, nullptr, g, s, Ls, x);
     }
 #pragma unroll
     for (int k = 0; k < 24; ++k) pn[k] = fma(be, pn[k], inv * (double)v[k]);
   }
-  store24<double>(pg, nullptr, g, s, Ls, pn);
+  store24<double, NT>(pg, nullptr, g, s, Ls, pn);
 }
 
-template <typename S>
+template <typename S, bool NT>
 __global__ void __launch_bounds__(256) k_block_update_xr(const BlockArgs b, Vec xv, Vec rv, Vec pv, Vec qv,
                                                           const double *scal, double *partial) {
   using R = typename Traits<S>::R;
@@ -1471,8 +1471,8 @@ __global__ void __launch_bounds__(256) k_block_update_xr(const BlockArgs b, Vec 
       x[k] += al * p[k];
       rr[k] -= al * q[k];
     }
-    store24<R>(reinterpret_cast<S *>(xv.data), xv.norm, o, s, Ls, x);
-    store24<R>(reinterpret_cast<S *>(rv.data), rv.norm, o, s, Ls, rr);
+    store24<R, NT>(reinterpret_cast<S *>(xv.data), xv.norm, o, s, Ls, x);
+    store24<R, NT>(reinterpret_cast<S *>(rv.data), rv.norm, o, s, Ls, rr);
     // the norm is taken of the stored (rounded) residual
     stored_values<S>(rr);
     R acc = 0;
@@ -1485,7 +1485,7 @@ __global__ void __launch_bounds__(256) k_block_update_xr(const BlockArgs b, Vec 
 
 // r -= alpha Ap with the partial |r|^2 (every iteration but the last, where
 // k_block_update_xr also updates x)
-template <typename S>
+template <typename S, bool NT>
 __global__ void __launch_bounds__(256) k_block_update_r(const BlockArgs b, Vec rv, Vec qv, const double *scal,
                                                         double *partial) {
   using R = typename Traits<S>::R;
@@ -1503,7 +1503,7 @@ __global__ void __launch_bounds__(256) k_block_update_r(const BlockArgs b, Vec r
     load24<R>(reinterpret_cast<const S *>(qv.data), qv.norm, o, s, Ls, q);
 #pragma unroll
     for (int k = 0; k < 24; ++k) rr[k] -= al * q[k];
-    store24<R>(reinterpret_cast<S *>(rv.data), rv.norm, o, s, Ls, rr);
+    store24<R, NT>(reinterpret_cast<S *>(rv.data), rv.norm, o, s, Ls, rr);
     stored_values<S>(rr);
     R acc = 0;
 #pragma unroll
@@ -1516,7 +1516,7 @@ __global__ void __launch_bounds__(256) k_block_update_r(const BlockArgs b, Vec r
 // x += alpha p, then p = r + beta p (the x update of k_block_update_xr moved
 // here, where p is read anyway), and M_phi p for the next first hop (from the
 // values as stored)
-template <typename S>
+template <typename S, bool NT>
 __global__ void __launch_bounds__(256) k_block_update_xp(const BlockArgs b, Vec xv, Vec pv, Vec mpv, Vec rv,
                                                          const double *scal, int first) {
   using R = typename Traits<S>::R;
@@ -1541,12 +1541,12 @@ __global__ void __launch_bounds__(256) k_block_update_xp(const BlockArgs b, Vec 
       x[k] += al * p[k];
       p[k] = rr[k] + be * p[k];
     }
-    store24<R>(reinterpret_cast<S *>(xv.data), xv.norm, o, s, Ls, x);
-    store24<R>(reinterpret_cast<S *>(pv.data), pv.norm, o, s, Ls, p);
+    store24<R, NT>(reinterpret_cast<S *>(xv.data), xv.norm, o, s, Ls, x);
+    store24<R, NT>(reinterpret_cast<S *>(pv.data), pv.norm, o, s, Ls, p);
     stored_values<S>(p);
   }
   block_mphi<R>(reinterpret_cast<R *>(smem), nthr, tid, s, Ls, b, p);
-  if (blk >= 0) store24<R>(reinterpret_cast<S *>(mpv.data), mpv.norm, o, s, Ls, p);
+  if (blk >= 0) store24<R, NT>(reinterpret_cast<S *>(mpv.data), mpv.norm, o, s, Ls, p);
 }
 
 // one workgroup per (block, rhs): a fixed-shape tree sum of that block's
@@ -1587,21 +1587,35 @@ static inline size_t block_lds_mphi(const BlockArgs &b) {
   return std::max(block_lds(b), (size_t)kRow * block_threads(b) * sizeof(typename Traits<S>::R));
 }
 
-#define MSPCG_PREC_SWITCH(prec, CALL)                 \
-  switch (prec) {                                     \
-    case MSPCG_F64: { using S = double; CALL; } break;   \
-    case MSPCG_F32: { using S = float; CALL; } break;    \
-    case MSPCG_F16: { using S = _Float16; CALL; } break; \
-    case MSPCG_BF16: { using S = bf16; CALL; } break;    \
-    default: return hipErrorInvalidValue;             \
+#define MSPCG_PREC_SWITCH(prec, ...)                        \
+  switch (prec) {                                           \
+    case MSPCG_F64: { using S = double; __VA_ARGS__; } break;   \
+    case MSPCG_F32: { using S = float; __VA_ARGS__; } break;    \
+    case MSPCG_F16: { using S = _Float16; __VA_ARGS__; } break; \
+    case MSPCG_BF16: { using S = bf16; __VA_ARGS__; } break;    \
+    default: return hipErrorInvalidValue;                   \
+  }
+
+// The lanes of the block kernels are packed: non-temporal stores (NT) only for rows
+// of whole 64-byte segments (see op5_kernel).  Ordinary -> non-temporal, us, 24^3 x 48, 16
+// blocks, gather and scatter alone in FP32, used: Ls 4 352 -> 315, 20 1739 -> 1668; not
+// used: Ls 2 217 -> 364, 5 489 -> 721, 13 1160 -> 1435.  (With one iteration on 16^3 x 32
+// at Ls 10 to 14 the two differ by 3%.)
+#define MSPCG_BLOCK_SWITCH(prec, Ls, ...)       \
+  if ((Ls) % 4 == 0) {                          \
+    constexpr bool NT = true;                   \
+    MSPCG_PREC_SWITCH(prec, __VA_ARGS__)        \
+  } else {                                      \
+    constexpr bool NT = false;                  \
+    MSPCG_PREC_SWITCH(prec, __VA_ARGS__)        \
   }
 
 hipError_t block_gather(int prec, const BlockArgs &b, const Vec &xs, const Vec &rs, const Vec &ps, const Vec &mps,
                         const Vec &rglob, const double *rr, double n_total, double *partial, hipStream_t st) {
   if (rglob.prec != MSPCG_F64 || block_threads(b) > 256) return hipErrorInvalidValue;
-  MSPCG_PREC_SWITCH(prec, hipLaunchKernelGGL(k_block_gather<S>, dim3(block_grid(b)), dim3(block_threads(b)),
-                                             block_lds_mphi<S>(b), st, b, xs, rs, ps, mps,
-                                             (const double *)rglob.data, rglob.stride, rr, n_total, partial));
+  MSPCG_BLOCK_SWITCH(prec, b.Ls, hipLaunchKernelGGL((k_block_gather<S, NT>), dim3(block_grid(b)),
+                     dim3(block_threads(b)), block_lds_mphi<S>(b), st, b, xs, rs, ps, mps,
+                     (const double *)rglob.data, rglob.stride, rr, n_total, partial));
   return hipGetLastError();
 }
 
@@ -1609,9 +1623,9 @@ hipError_t block_scatter(int prec, const BlockArgs &b, const Vec &zglob, const V
                          const double *scal, int mode, const Vec &rglob, const double *rr, double n_total,
                          double *partial, hipStream_t st) {
   if (zglob.prec != MSPCG_F64 || block_threads(b) > 256 || mode < 0 || mode > 2) return hipErrorInvalidValue;
-  MSPCG_PREC_SWITCH(prec, hipLaunchKernelGGL(k_block_scatter<S>, dim3(block_grid(b)), dim3(block_threads(b)),
-                                             block_lds(b), st, b, (double *)zglob.data, zglob.stride, xs, ps, scal,
-                                             mode, (const double *)rglob.data, rglob.stride, rr, n_total, partial));
+  MSPCG_BLOCK_SWITCH(prec, b.Ls, hipLaunchKernelGGL((k_block_scatter<S, NT>), dim3(block_grid(b)),
+                     dim3(block_threads(b)), block_lds(b), st, b, (double *)zglob.data, zglob.stride, xs, ps, scal,
+                     mode, (const double *)rglob.data, rglob.stride, rr, n_total, partial));
   return hipGetLastError();
 }
 
@@ -1619,9 +1633,9 @@ hipError_t block_scatter_xpay(int prec, const BlockArgs &b, const Vec &pglob, do
                               const Vec &ps, const double *scal, int mode, const double *rr, double n_total,
                               const double *alpha, const double *beta, int first, hipStream_t st) {
   if (pglob.prec != MSPCG_F64 || block_threads(b) > 256 || mode < 0 || mode > 2) return hipErrorInvalidValue;
-  MSPCG_PREC_SWITCH(prec, hipLaunchKernelGGL(k_block_scatter_xpay<S>, dim3(block_grid(b)), dim3(block_threads(b)), 0,
-                                             st, b, (double *)pglob.data, xglob, pglob.stride, xs, ps, scal, mode,
-                                             rr, n_total, alpha, beta, first));
+  MSPCG_BLOCK_SWITCH(prec, b.Ls, hipLaunchKernelGGL((k_block_scatter_xpay<S, NT>), dim3(block_grid(b)),
+                     dim3(block_threads(b)), 0, st, b, (double *)pglob.data, xglob, pglob.stride, xs, ps, scal, mode,
+                     rr, n_total, alpha, beta, first));
   return hipGetLastError();
 }
 
@@ -1636,24 +1650,24 @@ hipError_t block_scalars(int mode, const BlockArgs &b, const double *partial, do
 hipError_t block_update_xr(int prec, const BlockArgs &b, const Vec &x, const Vec &r, const Vec &p, const Vec &Ap,
                            const double *scal, double *partial, hipStream_t st) {
   if (block_threads(b) > 256) return hipErrorInvalidValue;
-  MSPCG_PREC_SWITCH(prec, hipLaunchKernelGGL(k_block_update_xr<S>, dim3(block_grid(b)), dim3(block_threads(b)),
-                                             block_lds(b), st, b, x, r, p, Ap, scal, partial));
+  MSPCG_BLOCK_SWITCH(prec, b.Ls, hipLaunchKernelGGL((k_block_update_xr<S, NT>), dim3(block_grid(b)),
+                     dim3(block_threads(b)), block_lds(b), st, b, x, r, p, Ap, scal, partial));
   return hipGetLastError();
 }
 
 hipError_t block_update_r(int prec, const BlockArgs &b, const Vec &r, const Vec &Ap, const double *scal,
                           double *partial, hipStream_t st) {
   if (block_threads(b) > 256) return hipErrorInvalidValue;
-  MSPCG_PREC_SWITCH(prec, hipLaunchKernelGGL(k_block_update_r<S>, dim3(block_grid(b)), dim3(block_threads(b)),
-                                             block_lds(b), st, b, r, Ap, scal, partial));
+  MSPCG_BLOCK_SWITCH(prec, b.Ls, hipLaunchKernelGGL((k_block_update_r<S, NT>), dim3(block_grid(b)),
+                     dim3(block_threads(b)), block_lds(b), st, b, r, Ap, scal, partial));
   return hipGetLastError();
 }
 
 hipError_t block_update_xp(int prec, const BlockArgs &b, const Vec &x, const Vec &p, const Vec &mp, const Vec &r,
                            const double *scal, int first, hipStream_t st) {
   if (block_threads(b) > 256) return hipErrorInvalidValue;
-  MSPCG_PREC_SWITCH(prec, hipLaunchKernelGGL(k_block_update_xp<S>, dim3(block_grid(b)), dim3(block_threads(b)),
-                                             block_lds_mphi<S>(b), st, b, x, p, mp, r, scal, first));
+  MSPCG_BLOCK_SWITCH(prec, b.Ls, hipLaunchKernelGGL((k_block_update_xp<S, NT>), dim3(block_grid(b)),
+                     dim3(block_threads(b)), block_lds_mphi<S>(b), st, b, x, p, mp, r, scal, first));
   return hipGetLastError();
 }
 

@@ -1,4 +1,4 @@
-"""Conversions and M_5^{-1} at fifth dimensions on both sides of the rules that choose
+"""Conversions, M_5^{-1} and the block kernels at fifth dimensions on both sides of the rules that choose
 their stores (rows of Ls x 16 bytes that are whole 128-byte lines, whole 64-byte
 segments, or neither; lanes that hold whole sites or are packed).
 
@@ -45,23 +45,42 @@ def test_conversions_and_m5inv_every_row(Ls, nrhs):
                 assert site_err(got[r], want) <= SITE_TOL[p], (PNAME[p], dagger)
 
 
+def time(torch, f):
+    """Median time of ten calls."""
+    f()
+    e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+    out = []
+    for _ in range(7):
+        e[0].record()
+        for _ in range(10):
+            f()
+        e[1].record()
+        torch.cuda.synchronize()
+        out.append(e[0].elapsed_time(e[1]))
+    return sorted(out)[3]
+
+
+def big_handle(Ls):
+    A = M.Action((24, 24, 24, 48), Ls, M5=1.8, mf=0.05, b=1.5, c=0.5)
+    return M.Handle(A, np.broadcast_to(np.eye(3, dtype=np.complex128), (A.V, 4, 3, 3)))
+
+
 @pytest.mark.parametrize("Ls", [2, 5, 24])
 def test_conversion_rate(Ls):
     torch = require_gpu()
-    A = M.Action((24, 24, 24, 48), Ls, M5=1.8, mf=0.05, b=1.5, c=0.5)
-    h = M.Handle(A, np.broadcast_to(np.eye(3, dtype=np.complex128), (A.V, 4, 3, 3)))
+    h = big_handle(Ls)
     a, b = h.field(M.F64, 1, 0), h.field(M.F64, 1, 0)
+    assert time(torch, lambda: h.convert(b, a)) <= 1.7 * time(torch, lambda: b.data.copy_(a.data))
 
-    def time(f):
-        e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
-        out = []
-        for _ in range(7):
-            e[0].record()
-            for _ in range(10):
-                f()
-            e[1].record()
-            torch.cuda.synchronize()
-            out.append(e[0].elapsed_time(e[1]))
-        return sorted(out)[3]
 
-    assert time(lambda: h.convert(b, a)) <= 1.7 * time(lambda: b.data.copy_(a.data))
+def test_block_gather_and_scatter_rate():
+    """Without inner iterations the preconditioner gathers and scatters: per 5D site at
+    most 1.55 times the time at Ls = 16 (1.2 to 1.3; stores of partial lines 1.7 to 2.2)."""
+    torch = require_gpu()
+    per_site = {}
+    for Ls in (2, 5, 16):
+        h = big_handle(Ls)
+        r, z = h.field(M.F64, 1, 0), h.field(M.F64, 1, 0)
+        r.data.normal_()
+        per_site[Ls] = time(torch, lambda: h.local_block_cg(z, r, (2, 2, 2, 2), 0, M.F32)) / Ls
+    assert per_site[2] <= 1.55 * per_site[16] and per_site[5] <= 1.55 * per_site[16], per_site
