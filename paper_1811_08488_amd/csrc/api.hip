@@ -1334,7 +1334,7 @@ mspcg_status solve(mspcg_handle *h, mspcg_field *x, const mspcg_field *b, const 
           // is never stored, and x waits for the update of p.  Vector passes of
           // a CG iteration outside the hops' own: 11 -> 7 (FP64 16^3 x 32 x 16,
           // with the host running ahead: 982 -> 804 us an iteration; 4^4 x 8,
-          // 11 -> 7 launches: 46 -> 25 us).
+          // 11 -> 7 launches: 90 -> 48 us).
           const Vec &to = h->tmp_o.v, &te = h->tmp_e.v;
           global_hop(h, MSPCG_F64, nrhs, 1, to, P, 0, 1, EPI_M5INV, -0.5, &h->x1, nullptr, nullptr, nullptr, st);
           const int parts2 = global_hop(h, MSPCG_F64, nrhs, 0, te, to, 0, 0, EPI_M5_OTHER, 0.5, nullptr, &P, part,
@@ -1766,8 +1766,9 @@ mspcg_status dwf_reconstruct(mspcg_handle *h, mspcg_field *psi_o, const mspcg_fi
     const int nrhs = psi_o->nrhs;
     if (psi_e->nrhs != nrhs || phi_o->nrhs != nrhs) fail(MSPCG_EINVAL, "nrhs mismatch");
     hipStream_t st = S(stream);
-    // psi_o = M_5^{-1} (phi_o - M^4_oe psi_e) = M_5^{-1} (phi_o + 1/2 H M_phi psi_e) in one hop; a caller whose psi_o shares memory with an input gets
-    // it by way of a temporary (the hop reads neighbours, and its first launch is repeated to tune it)
+    // psi_o = M_5^{-1} (phi_o - M^4_oe psi_e) = M_5^{-1} (phi_o + 1/2 H M_phi psi_e) in one hop; a caller whose
+    // psi_o shares memory with an input gets it by way of a temporary (the hop reads neighbours, and its first
+    // launch is repeated to tune it)
     const size_t bytes = (size_t)nrhs * h->Vh * h->par.Ls * 24 * sizeof(double);
     auto shares = [&](const mspcg_field *f) {
       const uintptr_t a = (uintptr_t)f->data, o = (uintptr_t)psi_o->data;
